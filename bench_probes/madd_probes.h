@@ -71,6 +71,21 @@ int32_t madd_stream_modes(int32_t mode, const void* a, void* b, int64_t bytes, v
  * launch fails. */
 int32_t madd_probe_bf16_rounding(uint64_t* counters, void* stream);
 
+/* The range-limited square root and division of csrc/exact.h against the
+ * general operations.
+ * counters: DEVICE array of 4 uint64 values owned by the caller, which the
+ * caller zeroes before the call; on completion they hold
+ *   [0] inputs +-0 and 2^-46 <= x < 2^127 where the square root differs,
+ *   [1] inputs 2^-126 <= |x| < 2^126 where the refined reciprocal is not the
+ *       one of x's significand, scaled,
+ *   [2] pairs of significands where the quotient differs (every denominator,
+ *       1024 numerators each: 512 hashed, 512 around it), and quotients of
+ *       -0 that are not -0,
+ *   [3] the number of bit patterns examined for [0] and [1] (2^32).
+ * Enqueued on `stream`.  Returns 0, -1 for a NULL pointer, -4 when the
+ * launch fails. */
+int32_t madd_check_exact_ops(uint64_t* counters, void* stream);
+
 /* madd_probe_delay: one wave on `stream` that sleeps `sleeps` times (each
  * s_sleep 127, about 8k cycles, ~3.5 us) and exits.  The benchmark enqueues
  * it ahead of a run of short steps so that the host has queued them all

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "exact.h"
 #include "madd_probes.h"
 
 namespace {
@@ -143,6 +144,45 @@ __global__ __launch_bounds__(256) void bf16_rounding_kernel(unsigned long long* 
   if (threadIdx.x == 0) atomicAdd(&c[3], 256ull * 256ull);  // this workgroup's inputs
 }
 
+// The range-limited square root, reciprocal and quotient of exact.h against
+// the general operations.  2^24 threads; each takes the 256 bit patterns from
+// 256 tid (square root, reciprocal) and the denominator significand tid / 2
+// with 512 numerators of its own (quotient).
+__global__ __launch_bounds__(256) void exact_ops_kernel(unsigned long long* c) {
+  using namespace madd_exact;
+  const uint32_t tid = blockIdx.x * 256u + threadIdx.x;
+  unsigned long long sbad = 0, rbad = 0, qbad = 0, seen = 0;
+  for (uint32_t j = 0; j < 256u; ++j) {
+    const uint32_t u = tid * 256u + j;
+    const float x = __uint_as_float(u);
+    if (u == 0u || u == 0x80000000u || (x >= 0x1p-46f && x < 0x1p127f))
+      sbad += __float_as_uint(sqrt_in_range(x)) != __float_as_uint(sqrtf(x));
+    const uint32_t e = (u >> 23) & 0xFFu;
+    if (e >= 1u && e < 253u) {  // 2^-126 <= |x| < 2^126
+      const float one = __uint_as_float((u & 0x807FFFFFu) | 0x3F800000u);
+      rbad += __float_as_uint(recip_in_range(x)) !=
+              __float_as_uint(ldexpf(recip_in_range(one), 127 - (int)e));
+    }
+    ++seen;
+  }
+  const float d = __uint_as_float(0x3F800000u | (tid >> 1));
+  const float r = recip_in_range(d);
+  for (uint32_t j = 0; j < 512u; ++j) {
+    // significands spread over [1, 2), then those next to the denominator's
+    const uint32_t m = (tid & 1u) ? hash32(tid * 512u + j) & 0x7FFFFFu
+                                  : ((tid >> 1) + j - 256u) & 0x7FFFFFu;
+    const float n = __uint_as_float(0x3F800000u | m);
+    qbad += quot_in_range(n, d, r) != n / d;
+  }
+  const float z = quot_in_range(-0.0f, d, r);
+  qbad += __float_as_uint(z) != 0x80000000u;
+  if (sbad) atomicAdd(&c[0], sbad);
+  if (rbad) atomicAdd(&c[1], rbad);
+  if (qbad) atomicAdd(&c[2], qbad);
+  for (int off = 32; off >= 1; off >>= 1) seen += __shfl_xor(seen, off);
+  if ((threadIdx.x & 63u) == 0u) atomicAdd(&c[3], seen);
+}
+
 // Plain streams in the step's access shape: a 256-thread workgroup owns one
 // 8 KiB tile and thread t moves 16 bytes at offset 16 t of each 4 KiB half,
 // non-temporal.  Read: the loads feed an XOR that is stored (to the sink's
@@ -205,6 +245,13 @@ extern "C" int32_t madd_probe_delay(int32_t sleeps, void* stream) {
 extern "C" int32_t madd_probe_bf16_rounding(uint64_t* counters, void* stream) {
   if (!counters) return -1;
   hipLaunchKernelGGL(bf16_rounding_kernel, dim3(65536), dim3(256), 0, (hipStream_t)stream,
+                     (unsigned long long*)counters);
+  return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+extern "C" int32_t madd_check_exact_ops(uint64_t* counters, void* stream) {
+  if (!counters) return -1;
+  hipLaunchKernelGGL(exact_ops_kernel, dim3(65536), dim3(256), 0, (hipStream_t)stream,
                      (unsigned long long*)counters);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }

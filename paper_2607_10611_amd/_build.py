@@ -24,6 +24,7 @@ ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "madd.hip")
 HDR = os.path.join(ROOT, "include", "madd.h")
 CACHE_HDR = os.path.join(PKG, "csrc", "table_cache.h")
+EXACT_HDR = os.path.join(PKG, "csrc", "exact.h")
 LIB = os.path.join(PKG, "libmadd.so")
 PROBE_DIR = os.path.join(ROOT, "bench_probes")
 PROBE_SRC = os.path.join(PROBE_DIR, "probes.hip")
@@ -64,7 +65,7 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmpdir, f"madd_part{k}.o") for k in range(NPARTS)]
         cmds = [[hipcc(), *compile_flags, *inc, f"-DMADD_PART={k}", "-c", "-o", objs[k], SRC]
                 for k in range(NPARTS)]
-        cmds.append([hipcc(), *HIPCC_FLAGS, "-I", PROBE_DIR, "-o", PROBE_LIB + ".tmp", PROBE_SRC])
+        cmds.append([hipcc(), *HIPCC_FLAGS, "-I", PROBE_DIR, "-I", os.path.join(PKG, "csrc"), "-o", PROBE_LIB + ".tmp", PROBE_SRC])
         workers = max(1, min(len(cmds), os.cpu_count() or 1))
         with ThreadPoolExecutor(workers) as ex:
             list(ex.map(lambda c: _run(c, verbose), cmds))
@@ -79,7 +80,7 @@ def is_stale() -> bool:
         if not os.path.exists(lib):
             return True
         t = os.path.getmtime(lib)
-        deps = (src, hdr, CACHE_HDR) if lib == LIB else (src, hdr)
+        deps = (src, hdr, EXACT_HDR, CACHE_HDR) if lib == LIB else (src, hdr, EXACT_HDR)
         if any(os.path.getmtime(p) > t for p in deps):
             return True
     return False

@@ -49,6 +49,7 @@
 #include <utility>
 #include <vector>
 
+#include "exact.h"
 #include "madd.h"
 #include "table_cache.h"
 
@@ -178,15 +179,15 @@ __device__ __forceinline__ float canon_nan(float x) {
   return (x == x) ? x : __uint_as_float(0x7FC00000u);
 }
 
-// Two values, `a` in the low half.
+// Two values, `a` in the low half, neither a NaN other than the canonical one
+// (whose sum with a draw keeps its high half).  The stochastic rule is its
+// integer definition, (bits + draw) >> 16: two additions at 2 cycles and a
+// byte permutation at 4 against two conversions at 8 each.
 __device__ __forceinline__ uint32_t enc_bf16x2(float a, float b, bool sr, uint32_t ra,
                                                uint32_t rb) {
-  if (sr) {
-    s2v r = __builtin_amdgcn_cvt_sr_bf16_f32(s2v{0, 0}, canon_nan(a), ra << 16, false);
-    r = __builtin_amdgcn_cvt_sr_bf16_f32(r, canon_nan(b), rb << 16, true);
-    return __builtin_bit_cast(uint32_t, r);
-  }
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{canon_nan(a), canon_nan(b)}, bf2v));
+  if (sr)
+    return __builtin_amdgcn_perm(__float_as_uint(b) + rb, __float_as_uint(a) + ra, 0x07060302u);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2v));
 }
 
 __device__ __forceinline__ uint32_t enc_bf16(float x, bool sr, uint32_t r16) {
@@ -384,20 +385,29 @@ __device__ __forceinline__ float clampf(float x, float lo, float hi) {
   return x < lo ? lo : (x > hi ? hi : x);  // NaN passes through
 }
 
+// The exponential moving averages of one element; `ge` receives the exponent
+// gradient.
+__device__ __forceinline__ void moments_elem(float w, float g, float& m, float& v, float& ve,
+                                             float& ge, const Scalars& s) {
+  const float LN2 = 0.693147182464599609375f;  // fp32(ln 2)
+  m = fmaf(s.B1, m, s.OMB1 * g);
+  v = fmaf(s.B2, v, s.OMB2 * (g * g));
+  ge = (LN2 * w) * g;
+  ve = fmaf(s.B2, ve, s.OMB2 * (ge * ge));
+}
+
+// The new weight from the updated moments, with the general square root and
+// division: every operand and hyper-parameter.
+//
 // CLAMP = false drops the g_max and w_max clamps; the host selects it only
 // when both bounds are +infinity, where the clamps are the identity (also for
 // NaN and infinite arguments), so the results are the same bits.
 template <bool CLAMP>
-__device__ __forceinline__ float step_elem(float w, float g, float& m, float& v, float& ve,
-                                           const Scalars& s) {
-  const float LN2 = 0.693147182464599609375f;  // fp32(ln 2)
+__device__ __forceinline__ float weight_elem(float w, float ge, float m, float v, float ve,
+                                             const Scalars& s) {
   // additive branch
-  m = fmaf(s.B1, m, s.OMB1 * g);
-  v = fmaf(s.B2, v, s.OMB2 * (g * g));
   const float ua = -((s.SA * m) / (sqrtf(v * s.IBC2) + s.EPS));
-  // multiplicative branch: exponent gradient and its second moment
-  const float ge = (LN2 * w) * g;
-  ve = fmaf(s.B2, ve, s.OMB2 * (ge * ge));
+  // multiplicative branch
   float r = ge / (sqrtf(ve * s.IBC2) + s.EPS);
   if (CLAMP) r = clampf(r, -s.GMAX, s.GMAX);
   const float ut = -(s.LRM * r);
@@ -408,6 +418,117 @@ __device__ __forceinline__ float step_elem(float w, float g, float& m, float& v,
   // combine, optional final clamp
   const float wn = fmaf(w, um, w) + ua;
   return CLAMP ? clampf(wn, -s.WMAX, s.WMAX) : wn;
+}
+
+template <bool CLAMP>
+__device__ __forceinline__ float step_elem(float w, float g, float& m, float& v, float& ve,
+                                           const Scalars& s) {
+  float ge;
+  moments_elem(w, g, m, v, ve, ge, s);
+  return weight_elem<CLAMP>(w, ge, m, v, ve, s);
+}
+
+// The same new weight from the range-limited square root and division of
+// exact.h (142 instead of 254 VALU cycles per element and wave, counted from
+// the measured rates of the instructions).  Powers of two move the
+// intermediates into their ranges: v IBC2 and v_e IBC2 are formed 2^80 times
+// larger (v's smallest denormal becomes 2^-69, and 2^48 the largest root
+// taken), the two numerators SA m and g_e are raised by 2^64, and the factors
+// leave again in operations that are there anyway (the addition of eps, the
+// product with eta_m, the final addition), so that each stays one rounding of
+// the same real number.  Where that is not so:
+//  * v IBC2 below 2^-126, which fp32 would round to a denormal: its root is
+//    below 2^-62 either way, less than half an ulp of eps >= 2^-38;
+//  * a quotient below 2^-126: g_e's then changes u_m below 2^-25, which leaves
+//    w + w u_m = w; m's changes |w'| >= 2^-100 by less than half an ulp;
+//  * |ut| below 2^-70: u_m stays below 2^-25 since tau >= 2^-40;
+//  * anything beyond a range: NaN, an infinity or a value above 2^60 in u_m's
+//    quotient or in w'.
+// So w' is the general path's, bit for bit, if `lo` (least |w'|) is at least
+// 2^-100 and `hi` (largest |w'| or |ut / rho|; NaN if any is) below 2^60,
+// and the hyper-parameters are in the ranges of `usable`.
+struct FastScalars {
+  float ibc2;  // 2^80 IBC2
+  float lrm;   // 2^-64 eta_m
+  bool usable;
+};
+
+// Uniform, on the scalar unit: positive floats order like their bits, and a
+// normal float times 2^k is k added to its exponent field.
+__device__ __forceinline__ FastScalars fast_scalars(const Scalars& s) {
+  auto within = [](float x, int lo, int hi) {  // 2^lo <= x < 2^hi
+    const uint32_t b = __float_as_uint(x), l = (uint32_t)(127 + lo) << 23,
+                   h = (uint32_t)(127 + hi) << 23;
+    return b - l < h - l;
+  };
+  const uint32_t lrm = __float_as_uint(s.LRM), alrm = lrm & 0x7FFFFFFFu;
+  FastScalars f;
+  f.ibc2 = __uint_as_float(__float_as_uint(s.IBC2) + (80u << 23));
+  f.lrm = alrm == 0u ? s.LRM : __uint_as_float(lrm - (64u << 23));
+  f.usable = within(s.EPS, -38, 20) && within(s.TAU, -40, 60) && within(s.IBC2, 0, 40) &&
+             (alrm == 0u || within(__uint_as_float(alrm), -60, 20)) &&
+             __float_as_uint(s.ULO) <= 0xBF7FFFF0u;  // r_max <= 1 - 2^-20
+  return f;
+}
+
+template <bool CLAMP>
+__device__ __forceinline__ float weight_elem_fast(float w, float ge, float m, float v, float ve,
+                                                  const Scalars& s, const FastScalars& f,
+                                                  float& lo, float& hi) {
+  using namespace madd_exact;
+  const float da = fmaf(sqrt_in_range(v * f.ibc2), kTwoM40, s.EPS);
+  const float qa = div_in_range((s.SA * m) * kTwo64, da);  // 2^64 u_a, negated
+  const float de = fmaf(sqrt_in_range(ve * f.ibc2), kTwoM40, s.EPS);
+  float r = div_in_range(ge * kTwo64, de);
+  if (CLAMP) r = clampf(r, -(s.GMAX * kTwo64), s.GMAX * kTwo64);
+  const float ut = -(f.lrm * r);
+  const float q = div_in_range(ut, max_abs(w, s.TAU));
+  const float um = __builtin_amdgcn_fmed3f(q, s.ULO, s.UHI);
+  const float wn = fmaf(qa, -kTwoM64, fmaf(w, um, w));
+  lo = fminf(fabsf(wn), lo);
+  hi = __builtin_elementwise_maximum(
+      __builtin_elementwise_maximum(__builtin_fabsf(q), __builtin_fabsf(wn)), hi);
+  return CLAMP ? clampf(wn, -s.WMAX, s.WMAX) : wn;
+}
+
+// The step of four elements: m, v, v_e updated in place, the new weights.
+// Where the range-limited arithmetic does not vouch for all four, the general
+// one takes them again.  CANON: NaNs of the moments and the new weights leave
+// as the canonical one (the range-limited path has none), for encoders that do
+// not look at NaNs.
+template <bool CLAMP, bool CANON_M, bool CANON_W>
+__device__ __forceinline__ void step_four(const float (&w)[4], f4 g, f4& m, f4& v, f4& ve,
+                                          float (&wn)[4], const Scalars& s) {
+  const FastScalars f = fast_scalars(s);
+  bool ok = false;
+  float ge[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float a = m[k], b = v[k], c = ve[k];
+    moments_elem(w[k], g[k], a, b, c, ge[k], s);
+    m[k] = a;
+    v[k] = b;
+    ve[k] = c;
+  }
+  if (f.usable) {  // uniform
+    float lo = madd_exact::kTwo60, hi = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      wn[k] = weight_elem_fast<CLAMP>(w[k], ge[k], m[k], v[k], ve[k], s, f, lo, hi);
+    ok = lo >= madd_exact::kTwoM100 && hi < madd_exact::kTwo60;
+  }
+  if (__builtin_expect(!ok, 0)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      wn[k] = weight_elem<CLAMP>(w[k], ge[k], m[k], v[k], ve[k], s);
+      if (CANON_W) wn[k] = canon_nan(wn[k]);
+      if (CANON_M) {
+        m[k] = canon_nan(m[k]);
+        v[k] = canon_nan(v[k]);
+        ve[k] = canon_nan(ve[k]);
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -570,7 +691,10 @@ __device__ __forceinline__ void store_quad(const Quad<WF>& q, const TensorDesc& 
 // given as values (block-scaled: payload value already multiplied by the
 // block's factor).
 __device__ __forceinline__ void store_copy_values(const float (&v)[4], uint16_t* copy, int64_t e) {
-  stg<u2>(copy + e, u2{enc_bf16x2(v[0], v[1], false, 0u, 0u), enc_bf16x2(v[2], v[3], false, 0u, 0u)});
+  float c[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c[k] = canon_nan(v[k]);
+  stg<u2>(copy + e, u2{enc_bf16x2(c[0], c[1], false, 0u, 0u), enc_bf16x2(c[2], c[3], false, 0u, 0u)});
 }
 
 template <int WF>
@@ -653,17 +777,12 @@ __device__ __forceinline__ void mdraws_any(uint64_t g0, const Scalars& s, MDraws
   }
 }
 
-template <int WF, bool SR, bool CLAMP>
+template <int WF, int SF, bool SR, bool CLAMP>
 __device__ __forceinline__ void step_quad(Quad<WF>& q, const uint32_t (&r)[4], const Scalars& s) {
-  float wn[4];
+  float w[4], wn[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    float m = q.m[k], v = q.v[k], ve = q.ve[k];
-    wn[k] = step_elem<CLAMP>(decode<WF>(q.w.code(k)), q.g[k], m, v, ve, s);
-    q.m[k] = m;
-    q.v[k] = v;
-    q.ve[k] = ve;
-  }
+  for (int k = 0; k < 4; ++k) w[k] = decode<WF>(q.w.code(k));
+  step_four<CLAMP, SF != SF_FP32, WF == WF_BF16>(w, q.g, q.m, q.v, q.ve, wn, s);
   if constexpr (WF == WF_BF16) {  // two codes per conversion
     q.w.raw = u2{enc_bf16x2(wn[0], wn[1], SR, r[0], r[1]), enc_bf16x2(wn[2], wn[3], SR, r[2], r[3])};
   } else {
@@ -709,15 +828,17 @@ __device__ __forceinline__ void step_scalar_range(const TensorDesc& d, int64_t b
   }
 }
 
-// Waves per SIMD the step kernel asks the compiler for: with bf16 moments
-// (rounded to nearest, no compute copy) the step is bound by VALU issue and
-// fits a fifth wave (at most 96 VGPRs) without spilling; elsewhere the
-// compiler's own choice stands (a tighter bound spills).
-template <int SF, bool COPY>
-constexpr int kStepWaves = (SF == SF_BF16 && !COPY) ? 5 : 1;
+// Waves per SIMD the step kernel asks the compiler for.  With stochastic bf16
+// moments (four draws per element) the compiler's own choice is 3 waves, too
+// few to keep HBM busy under their arithmetic; 4 (at most 128 VGPRs) take the
+// 1.1B list from 4.25 to 3.77-3.90 ms, 5 spill (4.83 ms).  The others fit 5
+// (at most 96 VGPRs) without spilling; with fp32 moments that is within the
+// noise of 4 (5.56 and 5.59 ms).
+template <int SF>
+constexpr int kStepWaves = SF == SF_BF16_SR ? 4 : 5;
 
 template <int WF, int GF, int SF, bool SR, bool CLAMP, bool COPY>
-__global__ __launch_bounds__(kThreads, (kStepWaves<SF, COPY>)) void madd_step_kernel(const TensorDesc* __restrict__ table,
+__global__ __launch_bounds__(kThreads, kStepWaves<SF>) void madd_step_kernel(const TensorDesc* __restrict__ table,
                                                              int ntab, TensorDesc single,
                                                              Scalars s_arg,
                                                              const Scalars* __restrict__ sdev) {
@@ -764,10 +885,10 @@ __global__ __launch_bounds__(kThreads, (kStepWaves<SF, COPY>)) void madd_step_ke
       uint32_t rA[4], rB[4];
       draws_aligned<SR>(gpair, s, rA, rB);
       mdraws_aligned<SF>(gpair, s, mA, mB);
-      step_quad<WF, SR, CLAMP>(qa, rA, s);
+      step_quad<WF, SF, SR, CLAMP>(qa, rA, s);
       store_quad<WF, SF>(qa, d, eA, mA);
       if (COPY && d.copy) store_copy<WF>(qa.w, d.copy, eA);
-      step_quad<WF, SR, CLAMP>(qb, rB, s);
+      step_quad<WF, SF, SR, CLAMP>(qb, rB, s);
       store_quad<WF, SF>(qb, d, eB, mB);
       if (COPY && d.copy) store_copy<WF>(qb.w, d.copy, eB);
       continue;
@@ -778,14 +899,14 @@ __global__ __launch_bounds__(kThreads, (kStepWaves<SF, COPY>)) void madd_step_ke
     draws_aligned<SR>(gpair, s, rA, rB);
     mdraws_aligned<SF>(gpair, s, mA, mB);
     if (fullA) {
-      step_quad<WF, SR, CLAMP>(qa, rA, s);
+      step_quad<WF, SF, SR, CLAMP>(qa, rA, s);
       store_quad<WF, SF>(qa, d, eA, mA);
       if (COPY && d.copy) store_copy<WF>(qa.w, d.copy, eA);
     } else if (eA < cend) {
       step_scalar_range<WF, GF, SF, SR, CLAMP, COPY>(d, eA, eA + kQuad < cend ? eA + kQuad : cend, s);
     }
     if (fullB) {
-      step_quad<WF, SR, CLAMP>(qb, rB, s);
+      step_quad<WF, SF, SR, CLAMP>(qb, rB, s);
       store_quad<WF, SF>(qb, d, eB, mB);
       if (COPY && d.copy) store_copy<WF>(qb.w, d.copy, eB);
     } else if (eB < cend) {
@@ -862,17 +983,16 @@ __device__ __forceinline__ uint32_t nv_block_code(uint32_t amax_bits, float st) 
   return enc_fp8<WF_E4M3>(__uint_as_float(amax_bits) / six_st, false, 0u);
 }
 
-template <int WF, bool SR, bool CLAMP>
+template <int WF, int SF, bool CLAMP>
 __device__ __forceinline__ uint32_t step_quad_unrounded(Quad<WF>& q, float sold, float (&wn)[4],
                                                         const Scalars& s) {
+  float w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = decode<WF>(q.w.code(k)) * sold;
+  step_four<CLAMP, SF != SF_FP32, false>(w, q.g, q.m, q.v, q.ve, wn, s);
   uint32_t amax = 0u;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    float m = q.m[k], v = q.v[k], ve = q.ve[k];
-    wn[k] = step_elem<CLAMP>(decode<WF>(q.w.code(k)) * sold, q.g[k], m, v, ve, s);
-    q.m[k] = m;
-    q.v[k] = v;
-    q.ve[k] = ve;
     const uint32_t ab = __float_as_uint(wn[k]) & 0x7FFFFFFFu;
     amax = ab > amax ? ab : amax;
   }
@@ -956,10 +1076,10 @@ __global__ __launch_bounds__(kThreads) void madd_step_block_kernel(
       mdraws_any<SF>((uint64_t)(d.gbase + eB), s, mB);
     }
     if (actA)
-      amaxA = step_quad_unrounded<WF, SR, CLAMP>(
+      amaxA = step_quad_unrounded<WF, SF, CLAMP>(
           qa, scale_value<WF>(load_scale<WF>(d.scales, (int64_t)((uint64_t)eA / kBlk)), st), wa, s);
     if (actB)
-      amaxB = step_quad_unrounded<WF, SR, CLAMP>(
+      amaxB = step_quad_unrounded<WF, SF, CLAMP>(
           qb, scale_value<WF>(load_scale<WF>(d.scales, (int64_t)((uint64_t)eB / kBlk)), st), wb, s);
     amaxA = block_amax<kLanes>(amaxA);
     amaxB = block_amax<kLanes>(amaxB);
@@ -1015,22 +1135,20 @@ __device__ __forceinline__ uint32_t nvcs_step_quad(const TensorDesc& d, int64_t 
   load_quad<WF_NVFP4, GF_FP32, SF>(q, d, e);
   const float den = scale_value<WF_NVFP4>(
       load_scale<WF_NVFP4>((const uint8_t*)d.scales + 4, (int64_t)((uint64_t)e / kNvBlock)), st);
-  f4 wn;
+  float w[4], wn[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = decode<WF_NVFP4>(q.w.code(k)) * den;
+  step_four<CLAMP, SF != SF_FP32, false>(w, q.g, q.m, q.v, q.ve, wn, s);
   uint32_t amax = 0u;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    float m = q.m[k], v = q.v[k], ve = q.ve[k];
-    wn[k] = step_elem<CLAMP>(decode<WF_NVFP4>(q.w.code(k)) * den, q.g[k], m, v, ve, s);
-    q.m[k] = m;
-    q.v[k] = v;
-    q.ve[k] = ve;
     const uint32_t ab = finite_abs_bits(wn[k]);
     amax = ab > amax ? ab : amax;
   }
   st4s<SF>(d.m, e, q.m, md.m);
   st4s<SF>(d.v, e, q.v, md.v);
   st4s<SF>(d.ve, e, q.ve, md.ve);
-  stg<f4>((float*)d.g + e, wn);  // w' replaces the gradient
+  stg<f4>((float*)d.g + e, f4{wn[0], wn[1], wn[2], wn[3]});  // w' replaces the gradient
   return amax;
 }
 

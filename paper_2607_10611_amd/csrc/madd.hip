@@ -807,6 +807,23 @@ __device__ __forceinline__ TensorDesc find_tensor(const TensorDesc* __restrict__
   return table[lo];
 }
 
+// The chunk of a workgroup.  Workgroups go round the 8 XCDs in launch order;
+// here each XCD takes runs of kXcdRun consecutive chunks (128 KiB of every
+// fp32 array), so that the XCDs stream from places apart instead of from
+// neighbouring lines of the same HBM pages.  Together with 3 waves per SIMD
+// this takes the 1.1B list with fp32 moments from 6.14-6.37 to 5.71-5.90 ms in
+// bf16 and from 5.75-6.09 to 5.29-5.36 ms in E4M3 (six buffer placements, in
+// turn in one process; runs of 8, 10, 12, 20, 24, 32, 48 and 64 chunks:
+// 5.82-6.42 and 5.22-5.69 ms); the lists of FP8 and NVFP4 masters from 4.30 to
+// 4.16 and from 4.17 to 4.06 ms, NVFP4 with current scaling 9.03 to 8.57 ms.
+constexpr uint32_t kXcds = 8, kXcdRun = 16;
+__device__ __forceinline__ int64_t xcd_chunk(uint32_t b, uint32_t n) {
+  constexpr uint32_t span = kXcds * kXcdRun;
+  if (b >= n - n % span) return b;  // the last, partial round
+  const uint32_t x = b % kXcds, r = b / kXcds;
+  return (int64_t)(r / kXcdRun) * span + x * kXcdRun + r % kXcdRun;
+}
+
 // Elements [b, e) one at a time (tails and unaligned buffers).
 template <int WF, int GF, int SF, bool SR, bool CLAMP, bool COPY>
 __device__ __forceinline__ void step_scalar_range(const TensorDesc& d, int64_t b, int64_t e,
@@ -828,22 +845,25 @@ __device__ __forceinline__ void step_scalar_range(const TensorDesc& d, int64_t b
   }
 }
 
-// Waves per SIMD the step kernel asks the compiler for.  With stochastic bf16
-// moments (four draws per element) the compiler's own choice is 3 waves, too
-// few to keep HBM busy under their arithmetic; 4 (at most 128 VGPRs) take the
-// 1.1B list from 4.25 to 3.77-3.90 ms, 5 spill (4.83 ms).  The others fit 5
-// (at most 96 VGPRs) without spilling; with fp32 moments that is within the
-// noise of 4 (5.56 and 5.59 ms).
+// Waves per SIMD of the step kernel.  With fp32 moments the step is bound by
+// HBM, and three waves' loads are enough to fill it; more only spread the
+// requests over more pages (1.1B list, bf16, in xcd_chunk's order: 2 waves
+// 5.74-5.80 ms, 3 waves 5.69, 4 waves 5.81-5.84, 5 waves 5.89-5.92).  bf16
+// moments halve the bytes, and the arithmetic between a wave's loads and
+// stores wants more of them: rounded to nearest 5 fit (at most 96 VGPRs;
+// GPT-2-small list 0.380 ms, 3 waves 0.404).  With stochastic rounding (four
+// draws per element) the compiler's own choice is 3 (4.25 ms); 4 (at most 128
+// VGPRs) take 3.79 ms, 5 spill (4.46 ms).
 template <int SF>
-constexpr int kStepWaves = SF == SF_BF16_SR ? 4 : 5;
+constexpr int kStepWaves = SF == SF_FP32 ? 3 : (SF == SF_BF16_SR ? 4 : 5);
 
 template <int WF, int GF, int SF, bool SR, bool CLAMP, bool COPY>
-__global__ __launch_bounds__(kThreads, kStepWaves<SF>) void madd_step_kernel(const TensorDesc* __restrict__ table,
-                                                             int ntab, TensorDesc single,
-                                                             Scalars s_arg,
-                                                             const Scalars* __restrict__ sdev) {
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kStepWaves<SF>, kStepWaves<SF>))) void madd_step_kernel(
+    const TensorDesc* __restrict__ table, int ntab, TensorDesc single, Scalars s_arg,
+    const Scalars* __restrict__ sdev) {
   const Scalars s = sdev ? *sdev : s_arg;  // uniform: device-resident hyper-parameters
-  const int64_t chunk = blockIdx.x;
+  const int64_t chunk = xcd_chunk(blockIdx.x, gridDim.x);
   const TensorDesc d = find_tensor(table, ntab, single, chunk);
   const int64_t c0 = (chunk - d.chunk0) * kChunk;
   const int64_t cend = (c0 + kChunk < d.n) ? c0 + kChunk : d.n;
@@ -1047,7 +1067,7 @@ __global__ __launch_bounds__(kThreads) void madd_step_block_kernel(
   const Scalars s = sdev ? *sdev : s_arg;
   constexpr int kBlk = block_len<WF>();
   constexpr int kLanes = kBlk / kQuad;
-  const int64_t chunk = blockIdx.x;
+  const int64_t chunk = xcd_chunk(blockIdx.x, gridDim.x);
   const TensorDesc d = find_tensor(table, ntab, single, chunk);
   const float st = WF == WF_NVFP4 ? *(const float*)d.scales : 1.0f;  // NVFP4 tensor scale
   const int64_t c0 = (chunk - d.chunk0) * kChunk;
@@ -1254,7 +1274,7 @@ __global__ __launch_bounds__(kThreads) void nvcs_step_kernel(const TensorDesc* _
                                                              const Scalars* __restrict__ sdev,
                                                              NvcsSpan sp) {
   const Scalars s = sdev ? *sdev : s_arg;
-  const int64_t b = blockIdx.x, n = sp.n1 + sp.n2;
+  const int64_t b = xcd_chunk(blockIdx.x, gridDim.x), n = sp.n1 + sp.n2;
   const int64_t before = (b * sp.n2) / n;  // pass-2 workgroups ahead of this one
   if (((b + 1) * sp.n2) / n > before)       // uniform per workgroup
     nvcs_pass2_chunk<SR, COPY>(table, ntab, single, sp.a2 + before, s);

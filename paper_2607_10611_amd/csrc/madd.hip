@@ -234,55 +234,73 @@ __device__ __forceinline__ float dec_fp8(uint32_t c) {
   return __uint_as_float(__float_as_uint(v) | ((c & 0x80u) << 24));
 }
 
-// Value-domain rounding onto a minifloat grid: scale |x| so that the grid
-// spacing of its binade is 1, round to an integer k (ties to even, or
-// stochastically), and assemble the code from the spacing exponent and k.
-// A k that reaches the next power of two lands on the next binade's code.
-// `val` receives the rounded magnitude k 2^se (exact), for callers that need
-// the stored value as well as its code.
-template <int M, int BIAS, int EMIN>
-__device__ __forceinline__ uint32_t round_mini(float a, bool sr, uint32_t r16, float& val) {
-  const int e = (int)((__float_as_uint(a) >> 23) & 0xFFu) - 127;
-  const int se = (e > EMIN ? e : EMIN) - M;  // exponent of the grid spacing
-  const float q = ldexpf(a, -se);            // exact; q < 2^(M+1)
-  float k;
-  if (sr) {
-    k = floorf(q);
-    const uint32_t f16 = (uint32_t)((q - k) * 65536.0f);  // exact
-    if (f16 + r16 >= 65536u) k += 1.0f;
-  } else {
-    k = rintf(q);
-  }
-  val = ldexpf(k, se);
-  return ((uint32_t)(se + M + BIAS - 1) << M) + (uint32_t)k;
-}
-template <int M, int BIAS, int EMIN>
-__device__ __forceinline__ uint32_t round_mini(float a, bool sr, uint32_t r16) {
-  float unused;
-  return round_mini<M, BIAS, EMIN>(a, sr, r16, unused);
-}
-
-// Branch-free: |x| is first clamped to the largest finite value (Inf and
-// finite overflow saturate; a NaN takes the clamp's value and is replaced by
-// the NaN code at the end).  The largest value is a grid point of its binade,
-// whose spacing then bounds every rounding of a clamped |x| by it, so no
-// code beyond the largest finite one can arise.
-// `val` receives the value of the returned code.
+// FP8 codes with gfx950's conversion instructions.  On every fp32 clamped to
+// the largest finite value they are the grid definitions bit for bit, also in
+// the subnormal binades (checked on all 2^32 inputs, the draws on both sides of
+// each input's threshold): RNE by v_cvt_pk_{fp8,bf8}_f32, and
+// v_cvt_sr_{fp8,bf8}_f32 with the draw in the high half of its random operand
+// compares it with the top 16 bits of the discarded fraction.  The codes of
+// NaN are left to the caller.  One conversion (8 cycles per wave, two codes per
+// instruction to nearest) replaces about nine integer and ldexp operations at 4.
 template <int WF>
-__device__ __forceinline__ uint32_t enc_fp8(float x, bool sr, uint32_t r16, float& val) {
-  using F = Mini<WF>;
-  const uint32_t sign = (__float_as_uint(x) >> 24) & 0x80u;
-  float a = fabsf(x);
-  a = a < F::MAXV ? a : F::MAXV;
-  float mag;
-  const uint32_t c = round_mini<F::M, F::BIAS, F::EMIN>(a, sr, r16, mag);
-  val = (x == x) ? __uint_as_float(__float_as_uint(mag) | (sign << 24)) : x;
-  return (x == x) ? (sign | c) : F::NANCODE;
+__device__ __forceinline__ float clamp_fp8(float x) {
+  return __builtin_amdgcn_fmed3f(x, -Mini<WF>::MAXV, Mini<WF>::MAXV);
+}
+template <int WF, int BYTE>
+__device__ __forceinline__ uint32_t cvt_sr_fp8(float a, uint32_t r16, uint32_t old) {
+  if constexpr (WF == WF_E4M3)
+    return (uint32_t)__builtin_amdgcn_cvt_sr_fp8_f32(a, (int)(r16 << 16), (int)old, BYTE);
+  else
+    return (uint32_t)__builtin_amdgcn_cvt_sr_bf8_f32(a, (int)(r16 << 16), (int)old, BYTE);
+}
+template <int WF, bool HIGH>
+__device__ __forceinline__ uint32_t cvt_pk_fp8(float a, float b, uint32_t old) {
+  if constexpr (WF == WF_E4M3)
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, HIGH);
+  else
+    return (uint32_t)__builtin_amdgcn_cvt_pk_bf8_f32(a, b, (int)old, HIGH);
 }
 template <int WF>
 __device__ __forceinline__ uint32_t enc_fp8(float x, bool sr, uint32_t r16) {
-  float unused;
-  return enc_fp8<WF>(x, sr, r16, unused);
+  const float a = clamp_fp8<WF>(x);
+  const uint32_t c = (sr ? cvt_sr_fp8<WF, 0>(a, r16, 0u) : cvt_pk_fp8<WF, false>(a, 0.0f, 0u)) & 0xFFu;
+  return (x == x) ? c : Mini<WF>::NANCODE;
+}
+// Four codes of non-NaN values, the first in the low byte.
+template <int WF, bool SR>
+__device__ __forceinline__ uint32_t enc_fp8x4(const float (&x)[4], const uint32_t (&r)[4]) {
+  const float a = clamp_fp8<WF>(x[0]), b = clamp_fp8<WF>(x[1]), c = clamp_fp8<WF>(x[2]),
+              d = clamp_fp8<WF>(x[3]);
+  if constexpr (SR) {
+    uint32_t q = cvt_sr_fp8<WF, 0>(a, r[0], 0u);
+    q = cvt_sr_fp8<WF, 1>(b, r[1], q);
+    q = cvt_sr_fp8<WF, 2>(c, r[2], q);
+    return cvt_sr_fp8<WF, 3>(d, r[3], q);
+  } else {
+    return cvt_pk_fp8<WF, true>(c, d, cvt_pk_fp8<WF, false>(a, b, 0u));
+  }
+}
+// The values of four codes.  The instruction gives NaN codes without a sign
+// the other NaN; a quad that holds one is decoded code by code.
+template <int WF>
+__device__ __forceinline__ void dec_fp8x4(uint32_t raw, float (&x)[4]) {
+  f2v a, b;
+  if constexpr (WF == WF_E4M3) {
+    a = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw, false);
+    b = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw, true);
+  } else {
+    a = __builtin_amdgcn_cvt_pk_f32_bf8((int)raw, false);
+    b = __builtin_amdgcn_cvt_pk_f32_bf8((int)raw, true);
+  }
+  x[0] = a.x;
+  x[1] = a.y;
+  x[2] = b.x;
+  x[3] = b.y;
+  constexpr uint32_t kToNan = (0x80u - (WF == WF_E4M3 ? 0x7Fu : 0x7Du)) * 0x01010101u;
+  if (__builtin_expect((((raw & 0x7F7F7F7Fu) + kToNan) & 0x80808080u) != 0u, 0)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = dec_fp8<WF>((raw >> (8 * k)) & 0xFFu);
+  }
 }
 
 // FP16 codes of the block scales (IEEE: RNE, overflow to Inf).
@@ -291,13 +309,7 @@ __device__ __forceinline__ float dec_fp16(uint32_t c) {
 }
 
 __device__ __forceinline__ uint32_t enc_fp16_rne(float x) {
-  const uint32_t sign = (__float_as_uint(x) >> 16) & 0x8000u;
-  const float a = fabsf(x);
-  if (!(a == a)) return 0x7E00u;
-  if (a >= 65536.0f) return sign | 0x7C00u;
-  uint32_t c = round_mini<10, 15, -14>(a, false, 0u);
-  c = c > 0x7C00u ? 0x7C00u : c;
-  return sign | c;
+  return (x == x) ? (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x) : 0x7E00u;
 }
 
 // MXFP4 (OCP Microscaling): E2M1 elements sharing an E8M0 power-of-two scale.
@@ -307,21 +319,36 @@ __device__ __forceinline__ float dec_e2m1(uint32_t c) {
   return (c & 8u) ? -mag : mag;
 }
 
-// x already divided by the block scale and finite; saturates at +-6 (6 is a
-// grid point, so rounding a clamped |x| never passes code 7).
-// `val` receives the value of the returned code.
-__device__ __forceinline__ uint32_t enc_e2m1(float x, bool sr, uint32_t r16, float& val) {
-  const uint32_t sign = (__float_as_uint(x) >> 28) & 0x8u;
-  float a = fabsf(x);
-  a = a < 6.0f ? a : 6.0f;
-  float mag;
-  const uint32_t c = round_mini<1, 1, 0>(a, sr, r16, mag);  // 1 mantissa bit, bias 1, min exponent 0
-  val = __uint_as_float(__float_as_uint(mag) | (sign << 28));
-  return sign | c;
+// E2M1 codes of values already divided by the block scale, not NaN, saturating
+// at +-6, with gfx950's conversions (checked like the FP8 ones).  The
+// stochastic one draws its second element from other bits of the random
+// operand, so each element takes one, with a zero beside it.
+__device__ __forceinline__ uint32_t cvt_sr_e2m1(float x, uint32_t r16) {  // code in bits 0-3
+  const float a = __builtin_amdgcn_fmed3f(x, -6.0f, 6.0f);
+  return __builtin_amdgcn_cvt_scalef32_sr_pk_fp4_f32(0u, f2v{a, 0.0f}, r16 << 16, 1.0f, 0);
 }
-__device__ __forceinline__ uint32_t enc_e2m1(float x, bool sr, uint32_t r16) {
-  float unused;
-  return enc_e2m1(x, sr, r16, unused);
+// Four codes, one per nibble, the first lowest.
+template <bool SR>
+__device__ __forceinline__ uint32_t enc_e2m1x4(const float (&x)[4], const uint32_t (&r)[4]) {
+  if constexpr (SR) {
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = cvt_sr_e2m1(x[k], r[k]);
+    const uint32_t lo = (c[0] & 0xFu) | ((c[1] << 4) & ~0xFu);  // byte 0 counts
+    const uint32_t hi = (c[2] & 0xFu) | ((c[3] << 4) & ~0xFu);
+    return __builtin_amdgcn_perm(hi, lo, 0x0C0C0400u);
+  } else {
+    const uint32_t q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[0], x[1], 1.0f, 0);
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, x[2], x[3], 1.0f, 1) & 0xFFFFu;
+  }
+}
+__device__ __forceinline__ void dec_e2m1x4(uint32_t raw, float (&x)[4]) {
+  const f2v a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(raw, 1.0f, 0);
+  const f2v b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(raw, 1.0f, 1);
+  x[0] = a.x;
+  x[1] = a.y;
+  x[2] = b.x;
+  x[3] = b.y;
 }
 
 // E8M0: 2^(c - 127); code 0 is the fp32 subnormal 2^-127; code 255 is NaN.
@@ -497,7 +524,7 @@ __device__ __forceinline__ float weight_elem_fast(float w, float ge, float m, fl
 // as the canonical one (the range-limited path has none), for encoders that do
 // not look at NaNs.
 template <bool CLAMP, bool CANON_M, bool CANON_W>
-__device__ __forceinline__ void step_four(const float (&w)[4], f4 g, f4& m, f4& v, f4& ve,
+__device__ __forceinline__ bool step_four(const float (&w)[4], f4 g, f4& m, f4& v, f4& ve,
                                           float (&wn)[4], const Scalars& s) {
   const FastScalars f = fast_scalars(s);
   bool ok = false;
@@ -529,6 +556,7 @@ __device__ __forceinline__ void step_four(const float (&w)[4], f4 g, f4& m, f4& 
       }
     }
   }
+  return !ok;
 }
 
 // ---------------------------------------------------------------------------
@@ -687,21 +715,32 @@ __device__ __forceinline__ void store_quad(const Quad<WF>& q, const TensorDesc& 
   st4s<SF>(d.ve, e, q.ve, md.ve);
 }
 
+// The values of four stored codes (before the block scale).
+template <int WF>
+__device__ __forceinline__ void decode_quad(const WQuad<WF>& w, float (&x)[4]) {
+  if constexpr (WF == WF_E4M3 || WF == WF_E5M2) {
+    dec_fp8x4<WF>(w.raw, x);
+  } else if constexpr (WF == WF_MXFP4 || WF == WF_NVFP4) {
+    dec_e2m1x4(w.raw, x);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = decode<WF>(w.code(k));
+  }
+}
+
 // The bf16 compute copy (rounded to nearest-even) of four new stored weights,
 // given as values (block-scaled: payload value already multiplied by the
-// block's factor).
+// block's factor), whose NaNs are the canonical one.
 __device__ __forceinline__ void store_copy_values(const float (&v)[4], uint16_t* copy, int64_t e) {
-  float c[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) c[k] = canon_nan(v[k]);
-  stg<u2>(copy + e, u2{enc_bf16x2(c[0], c[1], false, 0u, 0u), enc_bf16x2(c[2], c[3], false, 0u, 0u)});
+  stg<u2>(copy + e, u2{enc_bf16x2(v[0], v[1], false, 0u, 0u), enc_bf16x2(v[2], v[3], false, 0u, 0u)});
 }
 
 template <int WF>
 __device__ __forceinline__ void store_copy(const WQuad<WF>& w, uint16_t* copy, int64_t e) {
   float v[4];
+  decode_quad<WF>(w, v);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = decode<WF>(w.code(k));
+  for (int k = 0; k < 4; ++k) v[k] = canon_nan(v[k]);
   store_copy_values(v, copy, e);
 }
 
@@ -780,14 +819,21 @@ __device__ __forceinline__ void mdraws_any(uint64_t g0, const Scalars& s, MDraws
 template <int WF, int SF, bool SR, bool CLAMP>
 __device__ __forceinline__ void step_quad(Quad<WF>& q, const uint32_t (&r)[4], const Scalars& s) {
   float w[4], wn[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = decode<WF>(q.w.code(k));
-  step_four<CLAMP, SF != SF_FP32, WF == WF_BF16>(w, q.g, q.m, q.v, q.ve, wn, s);
+  decode_quad<WF>(q.w, w);
+  const bool general = step_four<CLAMP, SF != SF_FP32, WF == WF_BF16 || WF == WF_FP32>(
+      w, q.g, q.m, q.v, q.ve, wn, s);
   if constexpr (WF == WF_BF16) {  // two codes per conversion
     q.w.raw = u2{enc_bf16x2(wn[0], wn[1], SR, r[0], r[1]), enc_bf16x2(wn[2], wn[3], SR, r[2], r[3])};
+  } else if constexpr (WF == WF_FP32) {
+    q.w.raw = u4{__float_as_uint(wn[0]), __float_as_uint(wn[1]), __float_as_uint(wn[2]),
+                 __float_as_uint(wn[3])};
   } else {
+    q.w.raw = enc_fp8x4<WF, SR>(wn, r);
+    if (general) {  // the only path with NaNs
 #pragma unroll
-    for (int k = 0; k < 4; ++k) q.w.set(k, encode<WF>(wn[k], SR, r[k]));
+      for (int k = 0; k < 4; ++k)
+        if (!(wn[k] == wn[k])) q.w.set(k, Mini<WF>::NANCODE);
+    }
   }
 }
 
@@ -1007,8 +1053,9 @@ template <int WF, int SF, bool CLAMP>
 __device__ __forceinline__ uint32_t step_quad_unrounded(Quad<WF>& q, float sold, float (&wn)[4],
                                                         const Scalars& s) {
   float w[4];
+  decode_quad<WF>(q.w, w);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = decode<WF>(q.w.code(k)) * sold;
+  for (int k = 0; k < 4; ++k) w[k] *= sold;
   step_four<CLAMP, SF != SF_FP32, false>(w, q.g, q.m, q.v, q.ve, wn, s);
   uint32_t amax = 0u;
 #pragma unroll
@@ -1020,42 +1067,55 @@ __device__ __forceinline__ uint32_t step_quad_unrounded(Quad<WF>& q, float sold,
 }
 
 // Re-quantize four new weights of one block; `cv` receives their stored
-// values (payload value x scale) for the compute copy.
+// values (payload value x scale) for the compute copy.  One refined reciprocal
+// of the scale serves the four quotients where the range-limited division
+// holds (a numerator too small for it gives a quotient too small for any code
+// but zero, with the right sign); a block that holds a non-finite value has the
+// scale NaN and fixed codes.
 template <int WF, bool SR>
 __device__ __forceinline__ uint32_t requant_quad(Quad<WF>& q, const float (&wn)[4], uint32_t amax,
                                                  const uint32_t (&r)[4], float (&cv)[4], float st) {
+  using namespace madd_exact;
+  const float nan = __uint_as_float(0x7FC00000u);
+  float x[4];
   if constexpr (WF == WF_NVFP4) {
     const uint32_t sc = nv_block_code(amax, st);
     const float den = dec_fp8<WF_E4M3>(sc) * st;
-    const bool zero = sc == 0x7Fu || den == 0.0f;  // NaN block, or a factor of 0
+    if (__builtin_expect(den >= kTwoM60 && den <= kTwo60 && amax < 0x5D800000u, 1)) {  // 2^60
+      const float inv = recip_in_range(den);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float v;
-      const uint32_t c = enc_e2m1(wn[k] / den, SR, r[k], v);
-      q.w.set(k, zero ? 0u : c);
-      cv[k] = (zero ? 0.0f : v) * den;
+      for (int k = 0; k < 4; ++k) x[k] = quot_in_range(wn[k], den, inv);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = wn[k] / den;
     }
+    const bool bad = sc == 0x7Fu;
+    q.w.raw = (bad || den == 0.0f) ? 0u : enc_e2m1x4<SR>(x, r);  // NaN block, or a factor of 0
+    dec_e2m1x4(q.w.raw, x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cv[k] = bad ? nan : x[k] * den;
     return sc;
   } else if constexpr (WF == WF_MXFP4) {
     const uint32_t sc = mx_scale(amax);
     const float inv = mx_inv_scale(sc), X = dec_e8m0(sc);
+    const bool bad = sc == 0xFFu;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float v;
-      const uint32_t c = enc_e2m1(wn[k] * inv, SR, r[k], v);
-      q.w.set(k, sc == 0xFFu ? 0u : c);
-      cv[k] = (sc == 0xFFu ? 0.0f : v) * X;
-    }
+    for (int k = 0; k < 4; ++k) x[k] = wn[k] * inv;
+    q.w.raw = bad ? 0u : enc_e2m1x4<SR>(x, r);
+    dec_e2m1x4(q.w.raw, x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cv[k] = bad ? nan : x[k] * X;
     return sc;
   } else {
     const uint32_t sc = block_scale<WF>(amax);
-    const float sf = dec_fp16(sc);
+    const float sf = dec_fp16(sc), inv = recip_in_range(sf);
+    const bool bad = sc == 0x7E00u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float v;
-      q.w.set(k, enc_fp8<WF>(wn[k] / sf, SR, r[k], v));
-      cv[k] = v * sf;
-    }
+    for (int k = 0; k < 4; ++k) x[k] = quot_in_range(wn[k], sf, inv);
+    q.w.raw = bad ? Mini<WF>::NANCODE * 0x01010101u : enc_fp8x4<WF, SR>(x, r);
+    dec_fp8x4<WF>(q.w.raw, x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cv[k] = bad ? nan : x[k] * sf;
     return sc;
   }
 }
@@ -1156,8 +1216,9 @@ __device__ __forceinline__ uint32_t nvcs_step_quad(const TensorDesc& d, int64_t 
   const float den = scale_value<WF_NVFP4>(
       load_scale<WF_NVFP4>((const uint8_t*)d.scales + 4, (int64_t)((uint64_t)e / kNvBlock)), st);
   float w[4], wn[4];
+  decode_quad<WF_NVFP4>(q.w, w);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = decode<WF_NVFP4>(q.w.code(k)) * den;
+  for (int k = 0; k < 4; ++k) w[k] *= den;
   step_four<CLAMP, SF != SF_FP32, false>(w, q.g, q.m, q.v, q.ve, wn, s);
   uint32_t amax = 0u;
 #pragma unroll
@@ -1416,9 +1477,8 @@ __global__ __launch_bounds__(kThreads) void encode_mx_kernel(const float* __rest
     const uint32_t sc = mx_scale(amax);
     const float inv = mx_inv_scale(sc);
     for (int k = 0; k < kMxBlock; k += 2) {
-      const uint32_t lo = sc == 0xFFu ? 0u : enc_e2m1(xb[k] * inv, false, 0u);
-      const uint32_t hi = sc == 0xFFu ? 0u : enc_e2m1(xb[k + 1] * inv, false, 0u);
-      q[b * (kMxBlock / 2) + k / 2] = (uint8_t)(lo | (hi << 4));
+      const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, xb[k] * inv, xb[k + 1] * inv, 1.0f, 0);
+      q[b * (kMxBlock / 2) + k / 2] = sc == 0xFFu ? (uint8_t)0 : (uint8_t)c;
     }
     scales[b] = (uint8_t)sc;
   }
@@ -1474,9 +1534,8 @@ __global__ __launch_bounds__(kThreads) void encode_nv_kernel(const float* __rest
     const float den = dec_fp8<WF_E4M3>(sc) * st;
     const bool zero = sc == 0x7Fu || den == 0.0f;
     for (int k = 0; k < kNvBlock; k += 2) {
-      const uint32_t lo = zero ? 0u : enc_e2m1(xb[k] / den, false, 0u);
-      const uint32_t hi = zero ? 0u : enc_e2m1(xb[k + 1] / den, false, 0u);
-      q[b * (kNvBlock / 2) + k / 2] = (uint8_t)(lo | (hi << 4));
+      const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, xb[k] / den, xb[k + 1] / den, 1.0f, 0);
+      q[b * (kNvBlock / 2) + k / 2] = zero ? (uint8_t)0 : (uint8_t)c;
     }
     scales[head + b] = (uint8_t)sc;
   }

@@ -988,6 +988,10 @@ __attribute__((amdgpu_waves_per_eu(kStepWaves<SF>, kStepWaves<SF>))) void madd_s
 // so a block is never split and whole lane groups are active or inactive
 // together; every lane runs the shuffles and the draw exchange.
 template <int WF>
+constexpr bool fp4_weights() {
+  return WF == WF_MXFP4 || WF == WF_NVFP4;
+}
+template <int WF>
 constexpr int block_len() {
   return WF == WF_MXFP4 ? kMxBlock : (WF == WF_NVFP4 ? kNvBlock : kBlock);
 }
@@ -1399,33 +1403,119 @@ __global__ __launch_bounds__(kThreads) void zero_kernel(T* __restrict__ p, int64
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) p[i] = T(0);
 }
 
+#if MADD_IN_PART(0)
+// Set-up is bound by HBM: every access is a wave's contiguous span of 16 bytes
+// per lane (four elements), non-temporal except where the data is read again.
+
+// Zero the byte ranges [p, p + bytes) of the three moments, blockIdx.y choosing
+// one: 16-byte stores between the first and last 16-byte boundary, bytes
+// around them.
+constexpr int kZeroWords = 4;  // 16-byte words per thread and pass
+__global__ __launch_bounds__(kThreads) void zero3_kernel(void* p0, void* p1, void* p2,
+                                                         int64_t bytes) {
+  uint8_t* p = (uint8_t*)(blockIdx.y == 0 ? p0 : (blockIdx.y == 1 ? p1 : p2));
+  const int64_t lead = (int64_t)((16u - ((uintptr_t)p & 15u)) & 15u);
+  const int64_t head = lead < bytes ? lead : bytes, words = (bytes - head) >> 4;
+  const int64_t tail = head + (words << 4);
+  if (blockIdx.x == 0) {
+    if ((int)threadIdx.x < head) p[threadIdx.x] = 0;
+    if (tail + (int)threadIdx.x < bytes) p[tail + threadIdx.x] = 0;  // less than 16 bytes
+  }
+  u4* q = (u4*)(p + head);
+  const int64_t span = (int64_t)kThreads * kZeroWords, stride = (int64_t)gridDim.x * span;
+  for (int64_t i0 = (int64_t)blockIdx.x * span + threadIdx.x; i0 < words; i0 += stride) {
+#pragma unroll
+    for (int k = 0; k < kZeroWords; ++k)
+      if (i0 + k * kThreads < words) stg<u4>(q + i0 + k * kThreads, u4{0u, 0u, 0u, 0u});
+  }
+}
+
+// Four consecutive values of x and their codes; x and w at any address their
+// elements may have (the accesses of a quad are single instructions on gfx950
+// at every alignment).
+typedef f4 f4_any __attribute__((aligned(4)));
+template <int WF>
+struct CodeQuad {
+  typedef uint32_t T __attribute__((aligned(1)));
+};
+template <>
+struct CodeQuad<WF_BF16> {
+  typedef u2 T __attribute__((aligned(2)));
+};
+template <>
+struct CodeQuad<WF_FP32> {
+  typedef u4 T __attribute__((aligned(4)));
+};
+template <>
+struct CodeQuad<WF_MXFP4> {
+  typedef uint16_t T __attribute__((aligned(1)));
+};
+template <>
+struct CodeQuad<WF_NVFP4> {
+  typedef uint16_t T __attribute__((aligned(1)));
+};
+template <int WF>
+__device__ __forceinline__ void store_codes(void* w, int64_t e, typename CodeQuad<WF>::T c) {
+  uint8_t* p = (uint8_t*)w + (WF == WF_BF16 ? 2 * e
+                                            : (WF == WF_FP32 ? 4 * e : (fp4_weights<WF>() ? e >> 1 : e)));
+  __builtin_nontemporal_store(c, (GLOBAL typename CodeQuad<WF>::T*)p);
+}
+
 template <int WF>
 __global__ __launch_bounds__(kThreads) void encode_kernel(const float* __restrict__ x, void* w,
                                                           int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride)
-    st1w<WF>(w, i, encode<WF>(x[i], false, 0u));
-}
-
-// One thread per 128-element block.
-template <int WF>
-__global__ __launch_bounds__(kThreads) void encode_block_kernel(const float* __restrict__ x,
-                                                                uint8_t* q, uint16_t* scales,
-                                                                int64_t nblocks) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < nblocks; b += stride) {
-    const float* xb = x + b * kBlock;
-    uint32_t amax = 0u;
-    for (int k = 0; k < kBlock; ++k) {
-      const uint32_t ab = __float_as_uint(xb[k]) & 0x7FFFFFFFu;
-      amax = ab > amax ? ab : amax;
+  const int64_t stride = (int64_t)gridDim.x * kSub;
+  for (int64_t e = (int64_t)blockIdx.x * kSub + threadIdx.x * kQuad; e < n; e += stride) {
+    if (e + kQuad > n) {
+      for (int64_t i = e; i < n; ++i) st1w<WF>(w, i, encode<WF>(x[i], false, 0u));
+      break;
     }
-    const uint32_t sc = block_scale<WF>(amax);
-    const float sf = dec_fp16(sc);
-    for (int k = 0; k < kBlock; ++k) q[b * kBlock + k] = (uint8_t)enc_fp8<WF>(xb[k] / sf, false, 0u);
-    scales[b] = (uint16_t)sc;
+    const f4 v = __builtin_nontemporal_load((const GLOBAL f4_any*)(x + e));
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = encode<WF>(v[k], false, 0u);
+    if constexpr (WF == WF_BF16) store_codes<WF>(w, e, u2{c[0] | (c[1] << 16), c[2] | (c[3] << 16)});
+    else if constexpr (WF == WF_FP32) store_codes<WF>(w, e, u4{c[0], c[1], c[2], c[3]});
+    else store_codes<WF>(w, e, c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24));
   }
 }
+
+// Block-scaled formats: the lanes of a block share its largest |x| as in the
+// step kernel (n is a multiple of the block length, so they agree on every
+// branch).  One thread per block strides its lanes by a whole block: setting up
+// an 11008x4096 matrix (NVFP4, bf16 moments) took 0.313 ms that way and with
+// two-byte stores of the zeros; it takes 0.128 ms.
+// `scales` points at the block codes, `st` at NVFP4's tensor scale.
+template <int WF>
+__global__ __launch_bounds__(kThreads) void encode_block_kernel(const float* __restrict__ x,
+                                                                void* w, void* scales,
+                                                                const float* st_p, int64_t n) {
+  constexpr int kBlk = block_len<WF>(), kLanes = kBlk / kQuad;
+  const float st = WF == WF_NVFP4 ? *st_p : 1.0f;
+  const int64_t stride = (int64_t)gridDim.x * kSub;
+  for (int64_t e = (int64_t)blockIdx.x * kSub + threadIdx.x * kQuad; e < n; e += stride) {
+    const f4 v = __builtin_nontemporal_load((const GLOBAL f4_any*)(x + e));
+    const float wn[4] = {v.x, v.y, v.z, v.w};
+    uint32_t amax = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t ab = __float_as_uint(wn[k]) & 0x7FFFFFFFu;
+      amax = ab > amax ? ab : amax;
+    }
+    amax = block_amax<kLanes>(amax);
+    Quad<WF> q;
+    const uint32_t r[4] = {0u, 0u, 0u, 0u};
+    float cv[4];
+    const uint32_t sc = requant_quad<WF, false>(q, wn, amax, r, cv, st);
+    store_codes<WF>(w, e, (typename CodeQuad<WF>::T)q.w.raw);
+    if ((threadIdx.x & (kLanes - 1)) == 0u) {
+      const int64_t b = (int64_t)((uint64_t)e / kBlk);
+      if constexpr (fp4_weights<WF>()) ((uint8_t*)scales)[b] = (uint8_t)sc;
+      else ((uint16_t*)scales)[b] = (uint16_t)sc;
+    }
+  }
+}
+#endif  // MADD_IN_PART(0)
 
 #if MADD_IN_PART(0)
 // ---------------------------------------------------------------------------
@@ -1462,46 +1552,43 @@ __global__ __launch_bounds__(kThreads) void toy_grad_kernel(const void* w,
   }
 }
 
-// One thread per 32-element MXFP4 block.
-__global__ __launch_bounds__(kThreads) void encode_mx_kernel(const float* __restrict__ x,
-                                                             uint8_t* q, uint8_t* scales,
-                                                             int64_t nblocks) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < nblocks; b += stride) {
-    const float* xb = x + b * kMxBlock;
-    uint32_t amax = 0u;
-    for (int k = 0; k < kMxBlock; ++k) {
-      const uint32_t ab = __float_as_uint(xb[k]) & 0x7FFFFFFFu;
-      amax = ab > amax ? ab : amax;
-    }
-    const uint32_t sc = mx_scale(amax);
-    const float inv = mx_inv_scale(sc);
-    for (int k = 0; k < kMxBlock; k += 2) {
-      const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, xb[k] * inv, xb[k + 1] * inv, 1.0f, 0);
-      q[b * (kMxBlock / 2) + k / 2] = sc == 0xFFu ? (uint8_t)0 : (uint8_t)c;
-    }
-    scales[b] = (uint8_t)sc;
-  }
-}
-
 // NVFP4 encoding, three stages on the stream: the largest finite |x| of the
 // tensor into the scale array's first word (as fp32 bits; non-negative floats
-// order like their bits), that word turned into the per-tensor scale
-// st = amax / 2688 (1 when amax is 0), then one thread per 16-element block.
+// order like their bits; one atomic per workgroup), that word turned into the
+// per-tensor scale st = amax / 2688 (1 when amax is 0), then the blocks.  x is
+// read with temporal loads here: what the Infinity Cache keeps of it, the last
+// stage need not read from HBM again.
 __global__ __launch_bounds__(kThreads) void nv_amax_kernel(const float* __restrict__ x, int64_t n,
                                                            uint32_t* slot) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  __shared__ uint32_t part[kThreads / 64];
+  const int64_t stride = (int64_t)gridDim.x * kTile;
   uint32_t m = 0u;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
-    const uint32_t b = __float_as_uint(x[i]) & 0x7FFFFFFFu;
-    m = (b < 0x7F800000u && b > m) ? b : m;
+  auto take = [&m](f4 v) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t b = __float_as_uint(v[k]) & 0x7FFFFFFFu;
+      m = (b < 0x7F800000u && b > m) ? b : m;
+    }
+  };
+  for (int64_t e = (int64_t)blockIdx.x * kTile + threadIdx.x * kQuad; e < n; e += stride) {
+    const bool two = e + kSub < n;  // n is a multiple of 16: whole quads
+    const f4 a = *(const GLOBAL f4_any*)(x + e);
+    const f4 b = two ? (f4)*(const GLOBAL f4_any*)(x + e + kSub) : a;
+    take(a);
+    take(b);
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const uint32_t o = (uint32_t)__shfl_xor((int)m, off);
     m = o > m ? o : m;
   }
-  if ((threadIdx.x & 63u) == 0u && m != 0u) atomicMax(slot, m);
+  if ((threadIdx.x & 63u) == 0u) part[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 1; k < kThreads / 64; ++k) m = part[k] > m ? part[k] : m;
+    if (m != 0u) atomicMax(slot, m);
+  }
 }
 
 __global__ void nv_scale_kernel(uint32_t* slot) {
@@ -1516,30 +1603,6 @@ __global__ void nv_clear_kernel(uint32_t* slot, int words) {
   if (blockIdx.x == 0 && (int)threadIdx.x < words) slot[threadIdx.x] = 0u;
 }
 
-// `scales` holds st in its first word; the block codes start `head` bytes in
-// (4 for NVFP4, 8 for NVFP4 with current scaling).
-__global__ __launch_bounds__(kThreads) void encode_nv_kernel(const float* __restrict__ x,
-                                                             uint8_t* q, uint8_t* scales,
-                                                             int64_t nblocks, int head) {
-  const float st = *(const float*)scales;
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < nblocks; b += stride) {
-    const float* xb = x + b * kNvBlock;
-    uint32_t amax = 0u;
-    for (int k = 0; k < kNvBlock; ++k) {
-      const uint32_t ab = __float_as_uint(xb[k]) & 0x7FFFFFFFu;
-      amax = ab > amax ? ab : amax;
-    }
-    const uint32_t sc = nv_block_code(amax, st);
-    const float den = dec_fp8<WF_E4M3>(sc) * st;
-    const bool zero = sc == 0x7Fu || den == 0.0f;
-    for (int k = 0; k < kNvBlock; k += 2) {
-      const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, xb[k] / den, xb[k + 1] / den, 1.0f, 0);
-      q[b * (kNvBlock / 2) + k / 2] = zero ? (uint8_t)0 : (uint8_t)c;
-    }
-    scales[head + b] = (uint8_t)sc;
-  }
-}
 #endif  // MADD_IN_PART(0)
 
 // ---------------------------------------------------------------------------
@@ -2172,18 +2235,11 @@ int32_t madd_init_state(void* m, void* v, void* ve, int32_t sfmt, int64_t n, voi
     const uint64_t b[3] = {sb, sb, sb};
     if (!disjoint(p, b, 3)) return MADD_EINVAL;
   }
-  const int64_t want = (n + kThreads - 1) / kThreads;
-  const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
-  hipStream_t st = (hipStream_t)stream;
-  void* arr[3] = {m, v, ve};
-  for (void* p : arr) {
-    const int32_t rc =
-        sfmt == MADD_S_FP32
-            ? launch_k(zero_kernel<float>, dim3(grid), dim3(kThreads), st, (float*)p, n)
-            : launch_k(zero_kernel<uint16_t>, dim3(grid), dim3(kThreads), st, (uint16_t*)p, n);
-    if (rc != MADD_OK) return rc;
-  }
-  return MADD_OK;
+  const int64_t bytes = (sfmt == MADD_S_FP32 ? 4 : 2) * n;
+  const int64_t want = bytes / ((int64_t)kThreads * kZeroWords * 16) + 1;
+  const unsigned grid = (unsigned)(want < (1 << 20) ? want : (1 << 20));
+  return launch_k(zero3_kernel, dim3(grid, 3), dim3(kThreads), (hipStream_t)stream, m, v, ve,
+                  bytes);
 }
 
 int32_t madd_encode_weights(const float* x, void* w, int32_t wfmt, void* scales, int64_t n,
@@ -2208,40 +2264,28 @@ int32_t madd_encode_weights(const float* x, void* w, int32_t wfmt, void* scales,
     if (!disjoint(p, b, 3)) return MADD_EINVAL;
   }
   hipStream_t st = (hipStream_t)stream;
+  const int64_t want = (n + kSub - 1) / kSub;
+  const dim3 grid((unsigned)(want < (1 << 20) ? want : (1 << 20))), block(kThreads);
+  const float* none = nullptr;
   if (nv_fmt(wfmt)) {
     uint32_t* slot = (uint32_t*)scales;
     const int head = wfmt == MADD_W_NVFP4 ? 4 : 8;  // current scaling: st, amax word
-    const int64_t nb = n / kNvBlock;
-    const int64_t want_x = (n + kThreads - 1) / kThreads, want_b = (nb + kThreads - 1) / kThreads;
-    const unsigned grid_x = (unsigned)(want_x < 4096 ? want_x : 4096);
-    const unsigned grid_b = (unsigned)(want_b < 65536 ? want_b : 65536);
+    const int64_t tiles = (n + kTile - 1) / kTile;
+    const unsigned grid_x = (unsigned)(tiles < 2048 ? tiles : 2048);
     int32_t rc = launch_k(nv_clear_kernel, dim3(1), dim3(64), st, slot, head / 4);
     if (rc == MADD_OK) rc = launch_k(nv_amax_kernel, dim3(grid_x), dim3(kThreads), st, x, n, slot);
     if (rc == MADD_OK) rc = launch_k(nv_scale_kernel, dim3(1), dim3(64), st, slot);
     if (rc == MADD_OK)
-      rc = launch_k(encode_nv_kernel, dim3(grid_b), dim3(kThreads), st, x, (uint8_t*)w,
-                    (uint8_t*)scales, nb, head);
+      rc = launch_k(encode_block_kernel<WF_NVFP4>, grid, block, st, x, w,
+                    (void*)((uint8_t*)scales + head), (const float*)scales, n);
     return rc;
   }
-  if (wfmt == MADD_W_MXFP4) {
-    const int64_t nb = n / kMxBlock;
-    const int64_t want = (nb + kThreads - 1) / kThreads;
-    const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
-    return launch_k(encode_mx_kernel, dim3(grid), dim3(kThreads), st, x, (uint8_t*)w,
-                    (uint8_t*)scales, nb);
-  }
-  if (scales) {
-    const int64_t nb = n / kBlock;
-    const int64_t want = (nb + kThreads - 1) / kThreads;
-    const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
+  if (wfmt == MADD_W_MXFP4)
+    return launch_k(encode_block_kernel<WF_MXFP4>, grid, block, st, x, w, scales, none, n);
+  if (scales)
     return wfmt == MADD_W_FP8_E4M3
-               ? launch_k(encode_block_kernel<WF_E4M3>, dim3(grid), dim3(kThreads), st, x,
-                          (uint8_t*)w, (uint16_t*)scales, nb)
-               : launch_k(encode_block_kernel<WF_E5M2>, dim3(grid), dim3(kThreads), st, x,
-                          (uint8_t*)w, (uint16_t*)scales, nb);
-  }
-  const int64_t want = (n + kThreads - 1) / kThreads;
-  const dim3 grid((unsigned)(want < 65536 ? want : 65536)), block(kThreads);
+               ? launch_k(encode_block_kernel<WF_E4M3>, grid, block, st, x, w, scales, none, n)
+               : launch_k(encode_block_kernel<WF_E5M2>, grid, block, st, x, w, scales, none, n);
   switch (wfmt) {
     case MADD_W_BF16: return launch_k(encode_kernel<WF_BF16>, grid, block, st, x, w, n);
     case MADD_W_FP8_E4M3: return launch_k(encode_kernel<WF_E4M3>, grid, block, st, x, w, n);

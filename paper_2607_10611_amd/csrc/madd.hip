@@ -1361,19 +1361,17 @@ __device__ __forceinline__ float plain_elem(float w, float g, float lra, const S
   return clampf(fmaf(w, um, w) + ua, -s.WMAX, s.WMAX);
 }
 
-// Four consecutive elements per thread, grid-stride (diagnostic-sized work).
+// One element per thread, grid-stride: diagnostic-sized work is a chain of
+// memory latencies, and four elements in a row per thread were four of them.
 template <int WF, int GF, bool SR>
 __global__ __launch_bounds__(kThreads) void madd_plain_kernel(void* w, const void* g, int64_t n,
                                                               int64_t gbase, float lra,
                                                               Scalars s) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads * kQuad;
-  for (int64_t e0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kQuad; e0 < n; e0 += stride) {
-    const int64_t e1 = e0 + kQuad < n ? e0 + kQuad : n;
-    for (int64_t i = e0; i < e1; ++i) {
-      const float wn = plain_elem(decode<WF>(ld1w<WF>(w, i)), ld1g<GF>(g, i), lra, s);
-      const uint32_t r16 = SR ? draw_one((uint64_t)(gbase + i), s) : 0u;
-      st1w<WF>(w, i, encode<WF>(wn, SR, r16));
-    }
+  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
+    const float wn = plain_elem(decode<WF>(ld1w<WF>(w, i)), ld1g<GF>(g, i), lra, s);
+    const uint32_t r16 = SR ? draw_one((uint64_t)(gbase + i), s) : 0u;
+    st1w<WF>(w, i, encode<WF>(wn, SR, r16));
   }
 }
 
@@ -1532,6 +1530,13 @@ __global__ __launch_bounds__(kThreads) void toy_count_kernel(const int64_t* __re
 // fp32(4 / B): the derivative of (1/B) sum_k c_i (w_i - target_i)^4 over the
 // B sampled entries, in this fixed fp32 order.
 template <int WF>
+__device__ __forceinline__ float toy_grad_elem(uint32_t code, float target, float c, int32_t cnt,
+                                               float fob) {
+  const float d = decode<WF>(code) - target;
+  const float s = (fob * (float)cnt) * c;
+  return ((s * d) * d) * d;
+}
+template <int WF>
 __global__ __launch_bounds__(kThreads) void toy_grad_kernel(const void* w,
                                                             const float* __restrict__ target,
                                                             const float* __restrict__ c,
@@ -1539,10 +1544,47 @@ __global__ __launch_bounds__(kThreads) void toy_grad_kernel(const void* w,
                                                             int64_t n, float fob,
                                                             float* __restrict__ g) {
   const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
-    const float d = decode<WF>(ld1w<WF>(w, i)) - target[i];
-    const float s = (fob * (float)counts[i]) * c[i];
-    g[i] = ((s * d) * d) * d;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride)
+    g[i] = toy_grad_elem<WF>(ld1w<WF>(w, i), target[i], c[i], counts[i], fob);
+}
+
+// The same in one launch for the diagnostic's own sizes: a workgroup owns
+// kToyOwn entries, counts them in LDS over all samples, and writes their
+// counts and gradients.  Every workgroup reads all samples, so it is for
+// batches of up to kToyBatch (16 samples per thread, from L2 after the first
+// reader) and as many workgroups as the chip runs at once; beyond either,
+// clearing, counting by global atomics and the gradient take a launch each.
+// One iteration of the 4096-entry diagnostic with its step: 23.6 -> 19.0 us.
+constexpr int kToyThreads = 1024, kToyOwn = 512;
+constexpr int64_t kToyBatch = 16384, kToyGroups = 256;
+template <int WF>
+__global__ __launch_bounds__(kToyThreads) void toy_fused_kernel(
+    const void* w, const float* __restrict__ target, const float* __restrict__ c,
+    const int64_t* __restrict__ idx, int32_t batch, int64_t n, float fob,
+    int32_t* __restrict__ counts, float* __restrict__ g) {
+  __shared__ int32_t cnt[kToyOwn];
+  const int64_t first = (int64_t)blockIdx.x * kToyOwn, i = first + threadIdx.x;
+  const bool own = threadIdx.x < kToyOwn && i < n;
+  uint32_t code = 0u;
+  float t = 0.0f, ci = 0.0f;
+  if (own) {
+    code = ld1w<WF>(w, i);
+    t = target[i];
+    ci = c[i];
+  }
+  if (threadIdx.x < kToyOwn) cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t here = n - first < kToyOwn ? n - first : kToyOwn;  // entries of this workgroup
+#pragma unroll 4
+  for (int32_t k = threadIdx.x; k < batch; k += kToyThreads) {
+    const int64_t j = idx[k];
+    if (j >= first && j - first < here) atomicAdd(&cnt[j - first], 1);
+  }
+  __syncthreads();
+  if (own) {
+    const int32_t m = cnt[threadIdx.x];
+    counts[i] = m;
+    g[i] = toy_grad_elem<WF>(code, t, ci, m, fob);
   }
 }
 
@@ -2353,7 +2395,7 @@ int32_t madd_plain_step(void* w, int32_t wfmt, const void* g, int32_t gfmt, int6
     case MADD_W_FP8_E5M2: fn = pick_plain_gf<WF_E5M2>(gfmt, sr); break;
     default: fn = pick_plain_gf<WF_FP32>(gfmt, sr); break;
   }
-  const int64_t want = (n + (int64_t)kThreads * kQuad - 1) / ((int64_t)kThreads * kQuad);
+  const int64_t want = (n + kThreads - 1) / kThreads;
   const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
   return launch_k(fn, dim3(grid), dim3(kThreads), (hipStream_t)stream, w, g, n, index_base,
                   (float)hp->lr_add, s);
@@ -2374,6 +2416,22 @@ int32_t madd_toy_gradient(const void* w, int32_t wfmt, const float* target, cons
     if (!disjoint(p, b, 6)) return MADD_EINVAL;
   }
   hipStream_t st = (hipStream_t)stream;
+  const float fob = (float)(4.0 / (double)(batch > 0 ? batch : 1));
+  const int64_t groups = (n + kToyOwn - 1) / kToyOwn;
+  if (batch <= kToyBatch && groups <= kToyGroups) {
+    const dim3 grid((unsigned)groups), block(kToyThreads);
+    const int32_t nb = (int32_t)batch;
+    switch (wfmt) {
+      case MADD_W_BF16:
+        return launch_k(toy_fused_kernel<WF_BF16>, grid, block, st, w, target, c, idx, nb, n, fob, counts, g);
+      case MADD_W_FP8_E4M3:
+        return launch_k(toy_fused_kernel<WF_E4M3>, grid, block, st, w, target, c, idx, nb, n, fob, counts, g);
+      case MADD_W_FP8_E5M2:
+        return launch_k(toy_fused_kernel<WF_E5M2>, grid, block, st, w, target, c, idx, nb, n, fob, counts, g);
+      default:
+        return launch_k(toy_fused_kernel<WF_FP32>, grid, block, st, w, target, c, idx, nb, n, fob, counts, g);
+    }
+  }
   const int64_t want = (n + kThreads - 1) / kThreads;
   const dim3 grid((unsigned)(want < 65536 ? want : 65536)), block(kThreads);
   int32_t rc = launch_k(zero_kernel<uint32_t>, grid, block, st, (uint32_t*)counts, n);
@@ -2383,7 +2441,6 @@ int32_t madd_toy_gradient(const void* w, int32_t wfmt, const float* target, cons
                   batch, n, counts);
   }
   if (rc != MADD_OK) return rc;
-  const float fob = (float)(4.0 / (double)(batch > 0 ? batch : 1));
   switch (wfmt) {
     case MADD_W_BF16:
       return launch_k(toy_grad_kernel<WF_BF16>, grid, block, st, w, target, c, counts, n, fob, g);

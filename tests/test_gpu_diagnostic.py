@@ -135,3 +135,25 @@ def test_diagnostic_figure_outcomes():
     assert np.all(res[("mixed", "combined")]["w"][:h] != 0)
     assert np.all(res[("mixed", "multiplicative")]["w"][:h] == 0)
     assert half_err("combined", slice(h, None)) < 0.5 * half_err("additive", slice(h, None))
+
+
+@pytest.mark.parametrize("n,batch", [(1, 1), (511, 0), (512, 16384), (513, 1025), (512 * 256, 300),
+                                     (512 * 256 + 1, 300), (700, 16385)])
+def test_toy_gradient_on_both_sides_of_the_one_launch_rule(n, batch):
+    rng = np.random.default_rng(n + batch)
+    codes = oracle.encode_array("bf16", rng.normal(0, 2, n).astype(np.float32))
+    w = oracle.decode_array("bf16", codes).astype(np.float32)
+    target = rng.normal(0, 2, n).astype(np.float32)
+    c = np.ones(n, np.float32)
+    idx = rng.integers(-1, n + 1, batch)
+    counts = torch.full((n,), 77, dtype=torch.int32, device="cuda")
+    g = torch.full((n,), 1.0, device="cuda")
+    B.madd_toy_gradient(to_dev(codes), "bf16", to_dev(target), to_dev(c),
+                        torch.from_numpy(idx).cuda(), counts, g)
+    torch.cuda.synchronize()
+    ok = (idx >= 0) & (idx < n)
+    cnt = np.bincount(idx[ok], minlength=n)
+    assert np.array_equal(to_host(counts), cnt)
+    if batch:
+        want = oracle.toy_gradient(w, target, c, idx, batch)
+        assert np.array_equal(to_host(g).view(np.uint32), want.view(np.uint32))

@@ -70,8 +70,7 @@ constexpr int kThreads = 256;
 constexpr int kQuad = 4;                     // consecutive elements per thread and sub-tile
 constexpr int kSub = kThreads * kQuad;       // 1024 elements per sub-tile
 constexpr int kTile = 2 * kSub;              // sub-tiles A and B
-constexpr int kTilesPerChunk = 1;
-constexpr int64_t kChunk = (int64_t)kTile * kTilesPerChunk;
+constexpr int64_t kChunk = kTile;              // one workgroup's elements
 constexpr int kBlock = 128;                  // block-scaled FP8 block length
 constexpr int kMxBlock = 32;                 // MXFP4 block length (OCP MX)
 constexpr int kNvBlock = 16;                 // NVFP4 block length
@@ -1119,8 +1118,18 @@ __device__ __forceinline__ uint32_t requant_quad(Quad<WF>& q, const float (&wn)[
   }
 }
 
+// Waves per SIMD of the block kernel, which holds two quads and their block
+// factors through the re-quantization: 4 where its 128 VGPRs do (1.1B list, FP8
+// masters, bf16 moments: 3.59 ms with 4, 3.83 with the compiler's 3, 6.40,
+// spilling, with 5), 3 with the stochastic moments' draws (16 layers, FP8
+// masters: 2.99 ms, 4.44 with 4) and where fp32 moments bind it to HBM (4.46
+// and 4.60 ms).
+template <int SF>
+constexpr int kBlockWaves = SF == SF_BF16 ? 4 : 3;
+
 template <int WF, int GF, int SF, bool SR, bool CLAMP, bool COPY>
-__global__ __launch_bounds__(kThreads) void madd_step_block_kernel(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kBlockWaves<SF>, kBlockWaves<SF>))) void madd_step_block_kernel(
     const TensorDesc* __restrict__ table, int ntab, TensorDesc single, Scalars s_arg,
     const Scalars* __restrict__ sdev) {
   const Scalars s = sdev ? *sdev : s_arg;
@@ -1130,51 +1139,58 @@ __global__ __launch_bounds__(kThreads) void madd_step_block_kernel(
   const TensorDesc d = find_tensor(table, ntab, single, chunk);
   const float st = WF == WF_NVFP4 ? *(const float*)d.scales : 1.0f;  // NVFP4 tensor scale
   const int64_t c0 = (chunk - d.chunk0) * kChunk;
-  const int64_t cend = (c0 + kChunk < d.n) ? c0 + kChunk : d.n;
+  const int64_t eA = c0 + (int64_t)threadIdx.x * kQuad, eB = eA + kSub;
+  const uint64_t gpair = (uint64_t)(d.gbase + c0) + 8u * (threadIdx.x >> 1);
+  Quad<WF> qa, qb;
+  MDraws mA, mB;
+  uint32_t rA[4], rB[4];
+  // One quad from its loads on: step, block maximum, re-quantization, stores.
+  auto finish = [&](Quad<WF>& q, int64_t e, bool act, uint32_t code, const uint32_t (&r)[4],
+                    const MDraws& md) {
+    float wn[4], cv[4];
+    uint32_t amax = 0u;
+    if (act) amax = step_quad_unrounded<WF, SF, CLAMP>(q, scale_value<WF>(code, st), wn, s);
+    amax = block_amax<kLanes>(amax);
+    if (!act) return;
+    const uint32_t sc = requant_quad<WF, SR>(q, wn, amax, r, cv, st);
+    store_quad<WF, SF>(q, d, e, md);
+    if (COPY && d.copy) store_copy_values(cv, d.copy, e);
+    if ((threadIdx.x & (kLanes - 1)) == 0u) store_scale<WF>(d.scales, (int64_t)((uint64_t)e / kBlk), sc);
+  };
+  if (d.vec_ok && c0 + kTile <= d.n) {  // uniform: a whole tile, index base a multiple of 8
+    load_quad<WF, GF, SF>(qa, d, eA);
+    const uint32_t sA = load_scale<WF>(d.scales, (int64_t)((uint64_t)eA / kBlk));
+    load_quad<WF, GF, SF>(qb, d, eB);
+    const uint32_t sB = load_scale<WF>(d.scales, (int64_t)((uint64_t)eB / kBlk));
+    draws_aligned<SR>(gpair, s, rA, rB);
+    mdraws_aligned<SF>(gpair, s, mA, mB);
+    finish(qa, eA, true, sA, rA, mA);
+    __builtin_amdgcn_sched_barrier(0);  // interleaved with B's, the arithmetic spills
+    finish(qb, eB, true, sB, rB, mB);
+    return;
+  }
+  if (d.vec_ok) {
+    draws_aligned<SR>(gpair, s, rA, rB);
+    mdraws_aligned<SF>(gpair, s, mA, mB);
+  }
 #pragma unroll 1
-  for (int tile = 0; tile < kTilesPerChunk; ++tile) {
-    const int64_t tb = c0 + (int64_t)tile * kTile;
-    if (tb >= cend) break;
-    const int64_t eA = tb + (int64_t)threadIdx.x * kQuad, eB = eA + kSub;
-    const bool actA = eA < cend, actB = eB < cend;  // whole lane groups of a block agree
-    Quad<WF> qa, qb;
-    float wa[4], wb[4];
-    uint32_t amaxA = 0u, amaxB = 0u;
-    if (actA) load_quad<WF, GF, SF>(qa, d, eA);
-    if (actB) load_quad<WF, GF, SF>(qb, d, eB);
-    uint32_t rA[4], rB[4];
-    MDraws mA, mB;
-    if (d.vec_ok) {  // uniform: index base a multiple of 8
-      const uint64_t gpair = (uint64_t)(d.gbase + tb) + 8u * (threadIdx.x >> 1);
-      draws_aligned<SR>(gpair, s, rA, rB);
-      mdraws_aligned<SF>(gpair, s, mA, mB);
-    } else {
-      draws_any<SR>((uint64_t)(d.gbase + eA), s, rA);
-      draws_any<SR>((uint64_t)(d.gbase + eB), s, rB);
-      mdraws_any<SF>((uint64_t)(d.gbase + eA), s, mA);
-      mdraws_any<SF>((uint64_t)(d.gbase + eB), s, mB);
+  for (int half = 0; half < 2; ++half) {
+    const int64_t e = half ? eB : eA;
+    const bool act = e < d.n;  // whole lane groups of a block agree
+    if (!d.vec_ok) {
+      draws_any<SR>((uint64_t)(d.gbase + e), s, rA);
+      mdraws_any<SF>((uint64_t)(d.gbase + e), s, mA);
+    } else if (half) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rA[k] = rB[k];
+      mA = mB;
     }
-    if (actA)
-      amaxA = step_quad_unrounded<WF, SF, CLAMP>(
-          qa, scale_value<WF>(load_scale<WF>(d.scales, (int64_t)((uint64_t)eA / kBlk)), st), wa, s);
-    if (actB)
-      amaxB = step_quad_unrounded<WF, SF, CLAMP>(
-          qb, scale_value<WF>(load_scale<WF>(d.scales, (int64_t)((uint64_t)eB / kBlk)), st), wb, s);
-    amaxA = block_amax<kLanes>(amaxA);
-    amaxB = block_amax<kLanes>(amaxB);
-    float cv[4];
-    if (actA) {
-      const uint32_t sc = requant_quad<WF, SR>(qa, wa, amaxA, rA, cv, st);
-      store_quad<WF, SF>(qa, d, eA, mA);
-      if (COPY && d.copy) store_copy_values(cv, d.copy, eA);
-      if ((threadIdx.x & (kLanes - 1)) == 0u) store_scale<WF>(d.scales, (int64_t)((uint64_t)eA / kBlk), sc);
+    uint32_t code = 0u;
+    if (act) {
+      load_quad<WF, GF, SF>(qa, d, e);
+      code = load_scale<WF>(d.scales, (int64_t)((uint64_t)e / kBlk));
     }
-    if (actB) {
-      const uint32_t sc = requant_quad<WF, SR>(qb, wb, amaxB, rB, cv, st);
-      store_quad<WF, SF>(qb, d, eB, mB);
-      if (COPY && d.copy) store_copy_values(cv, d.copy, eB);
-      if ((threadIdx.x & (kLanes - 1)) == 0u) store_scale<WF>(d.scales, (int64_t)((uint64_t)eB / kBlk), sc);
-    }
+    finish(qa, e, act, code, rA, mA);
   }
 }
 
@@ -1208,12 +1224,10 @@ __device__ __forceinline__ uint32_t finite_abs_bits(float x) {
 }
 
 template <int SF, bool CLAMP>
-__device__ __forceinline__ uint32_t nvcs_step_quad(const TensorDesc& d, int64_t e, float st,
+__device__ __forceinline__ uint32_t nvcs_step_quad(Quad<WF_NVFP4>& q, uint32_t code,
+                                                   const TensorDesc& d, int64_t e, float st,
                                                    const MDraws& md, const Scalars& s) {
-  Quad<WF_NVFP4> q;
-  load_quad<WF_NVFP4, GF_FP32, SF>(q, d, e);
-  const float den = scale_value<WF_NVFP4>(
-      load_scale<WF_NVFP4>((const uint8_t*)d.scales + 4, (int64_t)((uint64_t)e / kNvBlock)), st);
+  const float den = scale_value<WF_NVFP4>(code, st);
   float w[4], wn[4];
   decode_quad<WF_NVFP4>(q.w, w);
 #pragma unroll
@@ -1243,6 +1257,19 @@ __device__ __forceinline__ void nvcs_pass1_chunk(const TensorDesc* __restrict__ 
   const int64_t c0 = (chunk - d.chunk0) * kChunk;
   const int64_t cend = (c0 + kChunk < d.n) ? c0 + kChunk : d.n;
   const int64_t eA = c0 + (int64_t)threadIdx.x * kQuad, eB = eA + kSub;
+  const bool actA = eA < cend, actB = eB < cend;  // n % 16 == 0: whole quads
+  // both quads' loads ahead of the arithmetic and stores of the first
+  Quad<WF_NVFP4> qa, qb;
+  uint32_t codeA = 0u, codeB = 0u;
+  const uint8_t* codes = (const uint8_t*)d.scales + 4;
+  if (actA) {
+    load_quad<WF_NVFP4, GF_FP32, SF>(qa, d, eA);
+    codeA = load_scale<WF_NVFP4>(codes, (int64_t)((uint64_t)eA / kNvBlock));
+  }
+  if (actB) {
+    load_quad<WF_NVFP4, GF_FP32, SF>(qb, d, eB);
+    codeB = load_scale<WF_NVFP4>(codes, (int64_t)((uint64_t)eB / kNvBlock));
+  }
   MDraws mA, mB;
   if (d.vec_ok) {  // uniform: index base a multiple of 8
     mdraws_aligned<SF>((uint64_t)(d.gbase + c0) + 8u * (threadIdx.x >> 1), s, mA, mB);
@@ -1251,9 +1278,9 @@ __device__ __forceinline__ void nvcs_pass1_chunk(const TensorDesc* __restrict__ 
     mdraws_any<SF>((uint64_t)(d.gbase + eB), s, mB);
   }
   uint32_t amax = 0u;
-  if (eA < cend) amax = nvcs_step_quad<SF, CLAMP>(d, eA, st, mA, s);  // n % 16 == 0: whole quads
-  if (eB < cend) {
-    const uint32_t b = nvcs_step_quad<SF, CLAMP>(d, eB, st, mB, s);
+  if (actA) amax = nvcs_step_quad<SF, CLAMP>(qa, codeA, d, eA, st, mA, s);
+  if (actB) {
+    const uint32_t b = nvcs_step_quad<SF, CLAMP>(qb, codeB, d, eB, st, mB, s);
     amax = b > amax ? b : amax;
   }
   // the wave's largest finite |w'|, folded into the tensor's amax word; a

@@ -14,16 +14,17 @@
 // tensor) and MXFP4 (E2M1 with an E8M0 scale per 32 elements).
 //
 // Layout of work: a launch covers a list of tensors.  The element space of
-// each tensor is cut into chunks; one workgroup (256 threads, four wave64s)
-// owns one chunk.  A chunk is made of tiles of 2048 elements, each split into
-// two sub-tiles of 1024; thread t handles the four consecutive elements
-// [4t, 4t+4) of both sub-tiles, so every load and store instruction of a
-// wave covers one contiguous span (1 KiB for fp32 arrays); a tile's loads
-// are issued together, and in whole tiles the arithmetic of sub-tile A waits
-// only for A's loads.  A workgroup finds its
-// tensor by a binary search over the descriptor table (uniform, scalar
-// loads).  Loads and stores of the streamed arrays are non-temporal global
-// accesses: nothing is reused within a step.
+// each tensor is cut into chunks of 2048 elements; one workgroup (256 threads,
+// four wave64s) owns one chunk, split into two sub-tiles of 1024; thread t
+// handles the four consecutive elements [4t, 4t+4) of both sub-tiles, so every
+// load and store instruction of a wave covers one contiguous span (1 KiB for
+// fp32 arrays); a tile's loads are issued together, and in whole tiles the
+// arithmetic of sub-tile A waits only for A's loads.  Chunks are dealt to the
+// XCDs in runs (xcd_chunk), and how many waves share a SIMD is chosen by what
+// bounds the kernel (kStepWaves, kBlockWaves).  A workgroup finds its tensor by
+// a binary search over the descriptor table (uniform, scalar loads).  Loads and
+// stores of the streamed arrays are non-temporal global accesses: nothing is
+// reused within a step.
 //
 // Random draws: the eight elements of an aligned group share one Philox
 // block.  Lanes 2k and 2k+1 cover one group of sub-tile A and one of
@@ -33,8 +34,8 @@
 //
 // Arithmetic: FP32, one fixed operation order (moments_elem, weight_elem), built with
 // -ffp-contract=off so that only the written fmaf calls fuse; division and
-// square root are the correctly rounded IEEE operations; fp32 denormals are
-// kept.  The result is bit-identical on every launch shape.
+// square root are correctly rounded (exact.h in range, the general operations
+// elsewhere); fp32 denormals are kept.  The result is bit-identical on every launch shape.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -2045,23 +2046,18 @@ int32_t launch_nvcs(const NvcsKernels& k, const TensorDesc* table, int ntab,
   return rc;
 }
 
-// Unscaled tensors may start anywhere, in memory and in the global index.  With
-// stochastic rounding their tiles start at the multiple of 8 of the global
-// index at or before element 0, so that the draws of a lane pair are one Philox
-// block everywhere: a tensor packed into a flat buffer at its global index is
-// then also 16-byte aligned again from its second quad on, and one that is not
-// pays for line crossings only (96 separately allocated tensors of odd sizes,
-// bf16: 0.83 -> 0.51 ms; 64 packed ones, E4M3 and bf16 moments: 0.42 -> 0.21-0.23,
-// both against one element at a time).  Without draws the tiles start where m
-// is 16-byte aligned.  Block-scaled tensors start aligned, at element 0.
-int32_t tile_shift(const void* scales, const void* m, int32_t sfmt, int64_t gbase, bool sr) {
-  if (scales) return 0;
-  if (sr || sfmt == MADD_S_BF16_SR) return (int32_t)(gbase & 7);
-  return (int32_t)(((uintptr_t)m & 15u) / (sfmt == MADD_S_FP32 ? 4u : 2u));
-}
-
+// Unscaled tensors may start anywhere, in memory and in the global index.
+// Their tiles start at the multiple of 8 of the global index at or before
+// element 0, so that the draws of a lane pair are one Philox block everywhere:
+// a tensor packed into a flat buffer at its global index is then also 16-byte
+// aligned again from its second quad on, and one that is not pays for line
+// crossings only (96 separately allocated tensors of odd sizes, bf16: 0.83 ->
+// 0.51 ms; 64 packed ones, E4M3 and bf16 moments: 0.42 -> 0.21-0.23, both
+// against one element at a time).  The rule looks at nothing that may change
+// from one step of a list to the next (rounding), so its cached table serves
+// them all.  Block-scaled tensors start aligned, at element 0.
 TensorDesc make_desc(void* w, void* scales, uint16_t* copy, const void* g, void* m, void* v,
-                     void* ve, int32_t sfmt, int64_t n, int64_t gbase, bool sr) {
+                     void* ve, int64_t n, int64_t gbase) {
   TensorDesc d;
   memset(&d, 0, sizeof(d));
   d.w = w;
@@ -2075,7 +2071,7 @@ TensorDesc make_desc(void* w, void* scales, uint16_t* copy, const void* g, void*
   d.gbase = gbase;
   d.chunk0 = 0;
   d.vec_ok = (gbase & 7) == 0;
-  d.shift = tile_shift(scales, m, sfmt, gbase, sr);
+  d.shift = scales ? 0 : (int32_t)(gbase & 7);
   return d;
 }
 
@@ -2204,7 +2200,7 @@ static int32_t multi_tensor_step(int32_t ntensors, void* const* w, const int32_t
         const bool is_blk = scales && scales[i];
         if (wfmt[i] == wf && (int)is_blk == blk && numel[i] > 0) {
           TensorDesc d = make_desc(w[i], is_blk ? scales[i] : nullptr, copy ? copy[i] : nullptr,
-                                   g[i], m[i], v[i], ve[i], sfmt, numel[i], gbase, sr);
+                                   g[i], m[i], v[i], ve[i], numel[i], gbase);
           d.chunk0 = nch;
           nch += chunks_of(numel[i] + d.shift);
           descs.push_back(d);
@@ -2385,7 +2381,7 @@ int32_t madd_step(void* w, int32_t wfmt, void* scales, uint16_t* copy, const voi
   if (n > INT64_MAX - index_base) return MADD_EINVAL;
   const Scalars s = make_scalars(*hp);
   const bool sr = hp->rounding == MADD_ROUND_SR;
-  const TensorDesc d = make_desc(w, scales, copy, g, m, v, ve, sfmt, n, index_base, sr);
+  const TensorDesc d = make_desc(w, scales, copy, g, m, v, ve, n, index_base);
   if (wfmt == MADD_W_NVFP4_CURRENT) {
     if (gfmt != MADD_G_FP32) return MADD_EINVAL;  // w' is written over the fp32 gradient
     const NvcsKernels k = pick_part9(sfmt, sr, needs_clamp(*hp), copy != nullptr);

@@ -260,3 +260,34 @@ def test_allocation_free_step_captures_a_list_never_stepped_before():
         B.madd_multi_tensor_step(tlb, h)
         torch.cuda.synchronize()
         assert_lists_equal(a, b, f"replay {r}")
+
+
+def test_a_list_stepped_with_one_rounding_captures_with_the_other():
+    """Tables are cached by content, which must not depend on the rounding:
+    a list of odd sizes stepped stochastically captures a step to nearest
+    (and the other way round)."""
+    sizes = [13, 2048 + 5, 700]
+    for first, second in (("sr", "rne"), ("rne", "sr")):
+        gen = torch.Generator(device="cuda")
+        lists = []
+        for _ in range(2):
+            gen.manual_seed(1)
+            w = [(0.02 * torch.randn(n, generator=gen, device="cuda")).bfloat16() for n in sizes]
+            g = [1e-3 * torch.randn(n, generator=gen, device="cuda") for n in sizes]
+            m, v, ve = ([torch.zeros(n, device="cuda") for n in sizes] for _ in range(3))
+            lists.append(([t.view(torch.int16) for t in w], g, m, v, ve))
+        tla, tlb = (B.TensorList(w, ["bf16"] * 3, g, m, v, ve) for w, g, m, v, ve in lists)
+        for tl in (tla, tlb):
+            B.madd_multi_tensor_step(tl, W.hparams("c2", step=1, rounding=first))
+        torch.cuda.synchronize()
+        h = W.hparams("c2", step=2, rounding=second)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            B.madd_multi_tensor_step(tla, h)
+        for r in range(3):
+            graph.replay()
+            B.madd_multi_tensor_step(tlb, h)
+            torch.cuda.synchronize()
+            for xs, ys in zip(lists[0], lists[1]):
+                for x, y in zip(xs, ys):
+                    assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (first, r)

@@ -11,7 +11,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, fields
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmadd.so")
@@ -91,6 +91,8 @@ class HParams:
                             int(self.seed) & (2**64 - 1), int(self.step))
 
 
+_HP_DEFAULTS = tuple((f.name, f.default) for f in fields(HParams))  # in the struct's order
+
 _lib = None
 
 
@@ -144,8 +146,9 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
+        # the handle of torch.cuda.current_stream() without the Stream object
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -210,7 +213,13 @@ def _hp(hp) -> madd_hparams:
     if isinstance(hp, madd_hparams):
         return hp
     if isinstance(hp, dict):
-        hp = HParams.from_dict(hp)
+        # HParams.from_dict(hp).to_c() without the object between
+        v = [hp.get(k, d) for k, d in _HP_DEFAULTS]
+        v[:11] = map(float, v[:11])
+        r, seed, step = v[12:]
+        v[11] = int(v[11])
+        return madd_hparams(*v[:12], ROUND[r] if isinstance(r, str) else int(r),
+                            int(seed) & (2**64 - 1), int(step))
     return hp.to_c()
 
 
@@ -346,11 +355,9 @@ def madd_multi_tensor_step(tl: TensorList, hp, gfmt: str = "fp32", index_base: i
     """One step over a TensorList (one launch per weight format)."""
     h = _hp(hp)
     tl.check_grads(gfmt)
-    PP = ctypes.POINTER(ctypes.c_void_p)
-    cast = lambda a: ctypes.cast(a, PP) if a is not None else None  # noqa: E731
     _check("madd_multi_tensor_step",
-           lib().madd_multi_tensor_step(tl.n, cast(tl.w), tl.wfmt, cast(tl.scales), cast(tl.copy),
-                                        cast(tl.g), GFMT[gfmt], cast(tl.m), cast(tl.v), cast(tl.ve),
+           lib().madd_multi_tensor_step(tl.n, tl.w, tl.wfmt, tl.scales, tl.copy,
+                                        tl.g, GFMT[gfmt], tl.m, tl.v, tl.ve,
                                         SFMT[tl.sfmt], tl.numel, int(index_base),
                                         ctypes.byref(h), _stream(stream)))
 
@@ -361,12 +368,10 @@ def madd_multi_tensor_step_noalloc(tl: TensorList, hp, gfmt: str = "fp32", index
     tables go to the library's fixed per-GPU array (at most 4096 tensors)."""
     h = _hp(hp)
     tl.check_grads(gfmt)
-    PP = ctypes.POINTER(ctypes.c_void_p)
-    cast = lambda a: ctypes.cast(a, PP) if a is not None else None  # noqa: E731
     _check("madd_multi_tensor_step_noalloc",
-           lib().madd_multi_tensor_step_noalloc(tl.n, cast(tl.w), tl.wfmt, cast(tl.scales),
-                                                cast(tl.copy), cast(tl.g), GFMT[gfmt],
-                                                cast(tl.m), cast(tl.v), cast(tl.ve),
+           lib().madd_multi_tensor_step_noalloc(tl.n, tl.w, tl.wfmt, tl.scales,
+                                                tl.copy, tl.g, GFMT[gfmt],
+                                                tl.m, tl.v, tl.ve,
                                                 SFMT[tl.sfmt], tl.numel, int(index_base),
                                                 ctypes.byref(h), _stream(stream)))
 
@@ -388,11 +393,9 @@ def madd_multi_tensor_step_dev(tl: TensorList, hp, dev_scalars, gfmt: str = "fp3
     h = _hp(hp)
     tl.check_grads(gfmt)
     _need("madd_multi_tensor_step_dev: dev_scalars", dev_scalars, int(lib().madd_scalars_bytes()))
-    PP = ctypes.POINTER(ctypes.c_void_p)
-    cast = lambda a: ctypes.cast(a, PP) if a is not None else None  # noqa: E731
     _check("madd_multi_tensor_step_dev",
-           lib().madd_multi_tensor_step_dev(tl.n, cast(tl.w), tl.wfmt, cast(tl.scales),
-                                            cast(tl.copy), cast(tl.g), GFMT[gfmt], cast(tl.m),
-                                            cast(tl.v), cast(tl.ve), SFMT[tl.sfmt], tl.numel,
+           lib().madd_multi_tensor_step_dev(tl.n, tl.w, tl.wfmt, tl.scales,
+                                            tl.copy, tl.g, GFMT[gfmt], tl.m,
+                                            tl.v, tl.ve, SFMT[tl.sfmt], tl.numel,
                                             int(index_base), ctypes.byref(h), _ptr(dev_scalars),
                                             _stream(stream)))

@@ -2009,6 +2009,10 @@ int32_t launch(step_fn fn, const TensorDesc* table, int ntab, const TensorDesc& 
 // pass 2 reading its group newest first) gained at most 0.3% more.  With
 // bf16 moments both passes are VALU bound, and the same groups take the
 // step from 39.3 ms (one group) to 38.8 ms (65536: 40.9; 98304: 43.7).
+//
+// With the range-limited arithmetic and xcd_chunk's order the 7B list takes
+// 42.1-42.5 ms (32768: 43.8-44.4), the 1.1B list 8.33 (32768: 7.79; 24576:
+// 7.99; 57344: 7.94; 81920: 8.17; 16384: 8.64): no one size is best for both.
 constexpr int64_t kNvcsGroupChunks = 40960;
 
 int32_t launch_nvcs(const NvcsKernels& k, const TensorDesc* table, int ntab,

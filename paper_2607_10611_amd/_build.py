@@ -25,6 +25,7 @@ SRC = os.path.join(PKG, "csrc", "madd.hip")
 HDR = os.path.join(ROOT, "include", "madd.h")
 CACHE_HDR = os.path.join(PKG, "csrc", "table_cache.h")
 EXACT_HDR = os.path.join(PKG, "csrc", "exact.h")
+ELEM_HDR = os.path.join(PKG, "csrc", "elem.h")
 LIB = os.path.join(PKG, "libmadd.so")
 PROBE_DIR = os.path.join(ROOT, "bench_probes")
 PROBE_SRC = os.path.join(PROBE_DIR, "probes.hip")
@@ -80,7 +81,7 @@ def is_stale() -> bool:
         if not os.path.exists(lib):
             return True
         t = os.path.getmtime(lib)
-        deps = (src, hdr, EXACT_HDR, CACHE_HDR) if lib == LIB else (src, hdr, EXACT_HDR)
+        deps = (src, hdr, EXACT_HDR, ELEM_HDR) + ((CACHE_HDR,) if lib == LIB else ())
         if any(os.path.getmtime(p) > t for p in deps):
             return True
     return False

@@ -37,6 +37,7 @@ sys.path.insert(0, ROOT)
 METRIC = "optimizer-step Gparams/s + achieved HBM GB/s (% of peak), 7B-shaped set"
 HBM_PEAK_GBS = 8000.0
 KERNEL_SRC = os.path.join(ROOT, "paper_2607_10611_amd", "csrc", "madd.hip")
+KERNEL_HDRS = [os.path.join(ROOT, "paper_2607_10611_amd", "csrc", h) for h in ("elem.h", "exact.h")]
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "madd_step_kernel_llama7b_bf16_sr_pmc.md")
 
 WBYTES = {"bf16": 2, "e4m3": 1, "e5m2": 1, "mxfp4": 0.5, "nvfp4": 0.5, "nvfp4_current": 0.5}
@@ -88,9 +89,10 @@ def log(msg: str):
 
 
 def kernel_sha() -> str:
-    """Hash of the kernel source's code: comments and blank lines stripped, so
-    that documentation edits do not invalidate a counter summary."""
-    src = open(KERNEL_SRC).read()
+    """Hash of the kernels' code (the source and the headers with device code):
+    comments and blank lines stripped, so that documentation edits do not
+    invalidate a counter summary."""
+    src = "\n".join(open(p).read() for p in (KERNEL_SRC, *KERNEL_HDRS))
     src = re.sub(r"/\*.*?\*/", "", src, flags=re.S)
     src = re.sub(r"//[^\n]*", "", src)
     code = "\n".join(line.rstrip() for line in src.splitlines() if line.strip())

@@ -70,6 +70,22 @@ def test_kernel_hash_ignores_comments_and_blank_lines(monkeypatch, tmp_path):
     assert bench.kernel_sha() != ha
 
 
+def test_kernel_hash_covers_the_headers_with_device_code(monkeypatch, tmp_path):
+    csrc = os.path.dirname(bench.KERNEL_SRC)
+    names = [os.path.basename(p) for p in (bench.KERNEL_SRC, *bench.KERNEL_HDRS)]
+    for h in names:
+        (tmp_path / h).write_text(open(os.path.join(csrc, h)).read())
+    monkeypatch.setattr(bench, "KERNEL_SRC", str(tmp_path / names[0]))
+    monkeypatch.setattr(bench, "KERNEL_HDRS", [str(tmp_path / h) for h in names[1:]])
+    for h in os.listdir(csrc):
+        if "__device__" not in open(os.path.join(csrc, h)).read():
+            continue
+        assert h in names
+        before = bench.kernel_sha()
+        (tmp_path / h).write_text((tmp_path / h).read_text() + "\nint added;\n")
+        assert bench.kernel_sha() != before, h
+
+
 def test_cpu_baseline_record():
     rec = bench.cpu_baseline("c5", 1 << 12, 2, "fp32", threads=2, seconds=0.0)
     assert rec["kind"] == "oracle" and rec["unit"] == "Gparam/s" and rec["cores"] == 2

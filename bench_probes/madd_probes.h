@@ -86,6 +86,19 @@ int32_t madd_probe_bf16_rounding(uint64_t* counters, void* stream);
  * launch fails. */
 int32_t madd_check_exact_ops(uint64_t* counters, void* stream);
 
+/* The step's arithmetic (csrc/elem.h) on `quads` groups of four elements, and
+ * which of its two forms each group took.
+ * w, g, m, v, ve: DEVICE fp32 arrays of 4 quads elements (weight values, the
+ * gradients, the moments before the step); scalars: DEVICE copy of
+ * madd_prepare_scalars' bytes; clamp: 1 applies g_max and w_max.
+ * got: the new weights as the kernels compute them; general: the same from the
+ * general square root and division; took: one byte per group, 1 if it fell
+ * back to those.  All owned by the caller.  Enqueued on `stream`.  Returns 0,
+ * -1 for an invalid argument, -4 when the launch fails. */
+int32_t madd_probe_step_path(const float* w, const float* g, const float* m, const float* v,
+                             const float* ve, int64_t quads, const void* scalars, int32_t clamp,
+                             float* got, float* general, uint8_t* took, void* stream);
+
 /* madd_probe_delay: one wave on `stream` that sleeps `sleeps` times (each
  * s_sleep 127, about 8k cycles, ~3.5 us) and exits.  The benchmark enqueues
  * it ahead of a run of short steps so that the host has queued them all

@@ -2,7 +2,7 @@
 optimizer step, include/madd.h) and, outside the package,
 ``bench_probes/libmadd_probes.so`` (measurement probes, not part of the
 optimizer: the streaming ceiling the benchmark reports beside the HBM peak,
-and the exhaustive check of the bf16 conversion instructions;
+and the device checks of the step's conversions and arithmetic;
 bench_probes/madd_probes.h).
 
 The flags are part of the numerical contract of the kernels:
@@ -29,9 +29,11 @@ ELEM_HDR = os.path.join(PKG, "csrc", "elem.h")
 LIB = os.path.join(PKG, "libmadd.so")
 PROBE_DIR = os.path.join(ROOT, "bench_probes")
 PROBE_SRC = os.path.join(PROBE_DIR, "probes.hip")
+CHECK_SRC = os.path.join(PROBE_DIR, "checks.hip")
 PROBE_HDR = os.path.join(PROBE_DIR, "madd_probes.h")
 PROBE_LIB = os.path.join(PROBE_DIR, "libmadd_probes.so")
-TARGETS = ((SRC, HDR, LIB), (PROBE_SRC, PROBE_HDR, PROBE_LIB))
+TARGETS = ((SRC, HDR, LIB), (PROBE_SRC, PROBE_HDR, PROBE_LIB),
+           (CHECK_SRC, PROBE_HDR, PROBE_LIB))
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -66,11 +68,16 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmpdir, f"madd_part{k}.o") for k in range(NPARTS)]
         cmds = [[hipcc(), *compile_flags, *inc, f"-DMADD_PART={k}", "-c", "-o", objs[k], SRC]
                 for k in range(NPARTS)]
-        cmds.append([hipcc(), *HIPCC_FLAGS, "-I", PROBE_DIR, "-I", os.path.join(PKG, "csrc"), "-o", PROBE_LIB + ".tmp", PROBE_SRC])
+        probe_inc = ["-I", PROBE_DIR, "-I", os.path.join(PKG, "csrc")]
+        probes = {src: os.path.join(tmpdir, os.path.basename(src) + ".o")
+                  for src in (PROBE_SRC, CHECK_SRC)}
+        cmds += [[hipcc(), *compile_flags, *probe_inc, "-c", "-o", obj, src]
+                 for src, obj in probes.items()]
         workers = max(1, min(len(cmds), os.cpu_count() or 1))
         with ThreadPoolExecutor(workers) as ex:
             list(ex.map(lambda c: _run(c, verbose), cmds))
         _run([hipcc(), *HIPCC_FLAGS, "-o", LIB + ".tmp", *objs], verbose)
+        _run([hipcc(), *HIPCC_FLAGS, "-o", PROBE_LIB + ".tmp", *probes.values()], verbose)
     os.replace(LIB + ".tmp", LIB)
     os.replace(PROBE_LIB + ".tmp", PROBE_LIB)
     return LIB

@@ -3,10 +3,11 @@ the line between that path and the general one (GPU).
 
 madd_check_exact_ops compares the operations with the general ones: the
 square root and the reciprocal on every fp32 of their ranges, the quotient on
-every denominator significand.  The step test puts operands and
-hyper-parameters on both sides of every bound the fast path is guarded by
-(weights, gradients and moments from the denormals to the largest values,
-zeros of both signs, infinities, NaN) and expects the oracle's bits.
+every denominator significand.  The step test mixes weights, gradients and
+moments from the denormals to the largest values, zeros of both signs,
+infinities and NaN within each group of four and expects the oracle's bits;
+most such groups take the general path (test_gpu_step_path.py places one
+operand at a time next to a bound and asserts which path its group takes).
 """
 import ctypes
 

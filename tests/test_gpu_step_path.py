@@ -159,6 +159,16 @@ CASES = {
                                m=sign(r, n) * log2_uniform(r, n, -99.99, -96) * ROOT1 / (SA * 0.9)), False),
     "u_a alone, below 2^-100": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
                                 m=sign(r, n) * log2_uniform(r, n, -126, -100.01) * ROOT1 / (SA * 0.9)), True),
+    # zero weights that nothing moves (padding rows, pruned weights): zeros of the right sign
+    "zero w and m": ({}, lambda r, n: {k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g", "m")}, False),
+    "zero w and m, no v": ({}, lambda r, n: dict({k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g", "m")},
+                                                 v=np.zeros(n), ve=np.zeros(n)), False),
+    "zero w, SA m rounds to 0": ({"lr_add": 2.0**-30}, lambda r, n: dict(
+        w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), m=sign(r, n) * log2_uniform(r, n, -149, -124)), False),
+    "zero w without additive rate": ({"lr_add": 0.0}, lambda r, n: dict(
+        w=np.where(r.random(n) < 0.5, -0.0, 0.0)), False),
+    "zero w, clamps": ({"g_max": 1.0, "w_max": 2.0}, lambda r, n: still(r, n, w=np.zeros(n)), False),
+    "zero w and m, infinite v": ({}, lambda r, n: still(r, n, w=np.zeros(n), v=np.full(n, np.inf)), True),
     # denominators of the relative update
     "w at tau": ({}, lambda r, n: dict(w=sign(r, n) * 1e-8 * log2_uniform(r, n, -2, 2)), False),
     "w at tau = 2^-40": ({"tau": 2.0**-40}, lambda r, n: dict(w=sign(r, n) * log2_uniform(r, n, -42, -38)), False),

@@ -39,3 +39,22 @@ def test_any_index_base(wfmt, sfmt, base):
         assert_state_equal(tag, h[0], hs.w, h[1], hs.m, h[2], hs.v, h[3], hs.ve, max_ulp=0)
         assert (to_host(ds.scales).view(hs.scales.dtype) == hs.scales).all(), tag
         assert_copy_equal(tag, ds, hs)
+
+
+@pytest.mark.parametrize("n", [16, 1040, 2048, 2048 + 272])
+def test_current_scaling_takes_the_largest_weight_from_any_wave(n):
+    rng = np.random.default_rng(n)
+    for at in sorted({0, 15, 255, 256, 700, 1023, 1024, 1300, 2047, 2048, n - 1}):
+        if at >= n:
+            continue
+        x = rng.normal(0, 0.02, n).astype(np.float32)
+        x[at] = -3.0
+        codes, scales = encode_nv_current(x)
+        hs, ds = HostState(codes, n, scales), DevState("nvfp4_current", codes, n, scales)
+        g = rng.normal(0, 1e-3, n).astype(np.float32)
+        hp = dict(W.DEFAULT_HPARAMS, rounding="sr", step=1)
+        gpu_step(ds, to_dev(g), hp)
+        oracle_step("nvfp4_current", hs, g, hp)
+        torch.cuda.synchronize()
+        assert (to_host(ds.scales) == hs.scales).all(), at
+        assert (ds.host()[0] == hs.w).all(), at

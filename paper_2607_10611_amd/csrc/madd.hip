@@ -994,9 +994,12 @@ __global__ __launch_bounds__(kThreads) void zero_kernel(T* __restrict__ p, int64
 // per lane (four elements), non-temporal except where the data is read again.
 
 // Zero the byte ranges [p, p + bytes) of the three moments, blockIdx.y choosing
-// one: 16-byte stores between the first and last 16-byte boundary, bytes
-// around them.
-constexpr int kZeroWords = 4;  // 16-byte words per thread and pass
+// one: a 16-byte store per thread and pass between the first and last 16-byte
+// boundary, bytes around them.  Four stores per thread, a workgroup's 4 KiB
+// apart, were slower than three launches of 4-byte temporal stores where the
+// moments are a few times the Infinity Cache (fp32, us: 45M elements 93, 88 and
+// 82 with one store; 200M 414, 434 and 360).  Temporal stores gain 2% more
+// here and lose 10% of a whole NVFP4 set-up, whose encoder reads x twice.
 __global__ __launch_bounds__(kThreads) void zero3_kernel(void* p0, void* p1, void* p2,
                                                          int64_t bytes) {
   uint8_t* p = (uint8_t*)(blockIdx.y == 0 ? p0 : (blockIdx.y == 1 ? p1 : p2));
@@ -1008,12 +1011,9 @@ __global__ __launch_bounds__(kThreads) void zero3_kernel(void* p0, void* p1, voi
     if (tail + (int)threadIdx.x < bytes) p[tail + threadIdx.x] = 0;  // less than 16 bytes
   }
   u4* q = (u4*)(p + head);
-  const int64_t span = (int64_t)kThreads * kZeroWords, stride = (int64_t)gridDim.x * span;
-  for (int64_t i0 = (int64_t)blockIdx.x * span + threadIdx.x; i0 < words; i0 += stride) {
-#pragma unroll
-    for (int k = 0; k < kZeroWords; ++k)
-      if (i0 + k * kThreads < words) stg<u4>(q + i0 + k * kThreads, u4{0u, 0u, 0u, 0u});
-  }
+  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < words; i += stride)
+    stg<u4>(q + i, u4{0u, 0u, 0u, 0u});
 }
 
 // Four consecutive values of x and their codes; x and w at any address their
@@ -1879,7 +1879,7 @@ int32_t madd_init_state(void* m, void* v, void* ve, int32_t sfmt, int64_t n, voi
     if (!disjoint(p, b, 3)) return MADD_EINVAL;
   }
   const int64_t bytes = (sfmt == MADD_S_FP32 ? 4 : 2) * n;
-  const int64_t want = bytes / ((int64_t)kThreads * kZeroWords * 16) + 1;
+  const int64_t want = bytes / ((int64_t)kThreads * 16) + 1;
   const unsigned grid = (unsigned)(want < (1 << 20) ? want : (1 << 20));
   return launch_k(zero3_kernel, dim3(grid, 3), dim3(kThreads), (hipStream_t)stream, m, v, ve,
                   bytes);

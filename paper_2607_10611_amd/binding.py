@@ -146,9 +146,13 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
-        # the handle of torch.cuda.current_stream() without the Stream object
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # the current stream's handle without a Stream object, where torch's
+        # internal call for it exists
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -147,12 +147,10 @@ def _ptr(t) -> int | None:
 def _stream(stream) -> int | None:
     if stream is None:
         import torch
-        # the current stream's handle without a Stream object, where torch's
-        # internal call for it exists
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is None:
+        try:  # torch's internal call: the current stream's handle without a Stream object
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:  # a torch without it
             return torch.cuda.current_stream().cuda_stream
-        return raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -381,9 +381,9 @@ __device__ __forceinline__ float weight_elem(float w, float ge, float m, float v
 //    quotient or in w'.
 // So w' is the general path's, bit for bit, if `lo` (least |w'|) is at least
 // 2^-100 and `hi` (largest |w'| or |ut / rho|; NaN if any is) below 2^60,
-// and the hyper-parameters are in the ranges of `usable`.  A zero weight with a
-// zero SA m may stay below 2^-100: g_e, r, ut and u_a are zeros of the general
-// path's signs, and w' with them.
+// and the hyper-parameters are in the ranges of `usable`.  A zero weight's w'
+// is u_a alone, which needs no bound but to be normal; with a zero SA m g_e, r,
+// ut and u_a are zeros of the general path's signs, and w' with them.
 struct FastScalars {
   float ibc2;  // 2^80 IBC2
   float lrm;   // 2^-64 eta_m
@@ -460,7 +460,9 @@ __device__ __forceinline__ bool step_four(const float (&w)[4], f4 g, f4& m, f4& 
       ok = hi < madd_exact::kTwo60;
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        ok = ok && (fabsf(wn[k]) >= madd_exact::kTwoM100 || (w[k] == 0.0f && s.SA * m[k] == 0.0f));
+        ok = ok && (fabsf(wn[k]) >= madd_exact::kTwoM100 ||
+                    (w[k] == 0.0f &&
+                     (fabsf(wn[k]) > madd_exact::kTwoM126 || s.SA * m[k] == 0.0f)));
     }
   }
   if (__builtin_expect(!ok, 0)) {

@@ -29,6 +29,7 @@ constexpr float kTwoM72 = kTwoM64 / 256.0f;
 constexpr float kTwo60 = 1152921504606846976.0f;
 constexpr float kTwoM60 = 1.0f / 1152921504606846976.0f;
 constexpr float kTwoM100 = kTwoM60 / 1099511627776.0f;
+constexpr float kTwoM126 = kTwoM64 * kTwoM60 / 4.0f;
 constexpr float kTwoM40 = 1.0f / 1099511627776.0f;
 
 // sqrt(x) for x = 0 or 2^-46 <= x < 2^127.  Smaller positive x give at most

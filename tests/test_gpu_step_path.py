@@ -155,10 +155,12 @@ CASES = {
     "tiny g": ({}, lambda r, n: dict(g=sign(r, n) * log2_uniform(r, n, -149, -70)), False),
     "tiny g, fresh v_e": ({}, lambda r, n: dict(g=sign(r, n) * log2_uniform(r, n, -149, -70),
                                                ve=np.zeros(n)), False),
-    "u_a alone, from 2^-100": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
-                               m=sign(r, n) * log2_uniform(r, n, -99.99, -96) * ROOT1 / (SA * 0.9)), False),
-    "u_a alone, below 2^-100": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
-                                m=sign(r, n) * log2_uniform(r, n, -126, -100.01) * ROOT1 / (SA * 0.9)), True),
+    "u_a alone, from 2^-126": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
+                               m=sign(r, n) * log2_uniform(r, n, -125.99, -96) * ROOT1 / (SA * 0.9)), False),
+    "denormal u_a alone": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
+                           m=sign(r, n) * log2_uniform(r, n, -134, -126.01) * ROOT1 / (SA * 0.9)), True),
+    "u_a of a denormal SA m": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n),
+                               v=log2_uniform(r, n, -46, -40), m=sign(r, n) * log2_uniform(r, n, -133, -125)), False),
     # zero weights that nothing moves (padding rows, pruned weights): zeros of the right sign
     "zero w and m": ({}, lambda r, n: {k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g", "m")}, False),
     "zero w and m, no v": ({}, lambda r, n: dict({k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g", "m")},

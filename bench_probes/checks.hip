@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void step_path_kernel(
     float mk = m[4 * q + k], vk = v[4 * q + k], vek = ve[4 * q + k], ge;
     moments_elem(w4[k], g4[k], mk, vk, vek, ge, s);
     got[4 * q + k] = wn[k];
-    general[4 * q + k] = weight_elem<CLAMP>(w4[k], ge, mk, vk, vek, s);
+    general[4 * q + k] = weight_elem<CLAMP>(w4[k], ge, add_update(mk, vk, s), vek, s);
   }
 }
 

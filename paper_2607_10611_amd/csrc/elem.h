@@ -340,16 +340,17 @@ __device__ __forceinline__ void moments_elem(float w, float g, float& m, float& 
 }
 
 // The new weight from the updated moments, with the general square root and
-// division: every operand and hyper-parameter.
+// division: every operand and hyper-parameter.  u_a, then the weight it enters.
 //
 // CLAMP = false drops the g_max and w_max clamps; the host selects it only
 // when both bounds are +infinity, where the clamps are the identity (also for
 // NaN and infinite arguments), so the results are the same bits.
+__device__ __forceinline__ float add_update(float m, float v, const Scalars& s) {
+  return -((s.SA * m) / (sqrtf(v * s.IBC2) + s.EPS));
+}
 template <bool CLAMP>
-__device__ __forceinline__ float weight_elem(float w, float ge, float m, float v, float ve,
+__device__ __forceinline__ float weight_elem(float w, float ge, float ua, float ve,
                                              const Scalars& s) {
-  // additive branch
-  const float ua = -((s.SA * m) / (sqrtf(v * s.IBC2) + s.EPS));
   // multiplicative branch
   float r = ge / (sqrtf(ve * s.IBC2) + s.EPS);
   if (CLAMP) r = clampf(r, -s.GMAX, s.GMAX);
@@ -382,8 +383,9 @@ __device__ __forceinline__ float weight_elem(float w, float ge, float m, float v
 // So w' is the general path's, bit for bit, if `lo` (least |w'|) is at least
 // 2^-100 and `hi` (largest |w'| or |ut / rho|; NaN if any is) below 2^60,
 // and the hyper-parameters are in the ranges of `usable`.  A zero weight's w'
-// is u_a alone, which needs no bound but to be normal; with a zero SA m g_e, r,
-// ut and u_a are zeros of the general path's signs, and w' with them.
+// is u_a alone, which needs no bound but to be normal, w + w u_m being a zero of
+// ut's sign; with a zero SA m all of g_e, r, ut and u_a are zeros of the general
+// path's signs, and w' with them.
 struct FastScalars {
   float ibc2;  // 2^80 IBC2
   float lrm;   // 2^-64 eta_m
@@ -430,7 +432,7 @@ __device__ __forceinline__ float weight_elem_fast(float w, float ge, float m, fl
 
 // The step of four elements: m, v, v_e updated in place, the new weights.
 // Where the range-limited arithmetic does not vouch for all four, the general
-// one takes them again.  CANON: NaNs of the moments and the new weights leave
+// one takes them again; true if it did.  CANON: NaNs of the moments and the new weights leave
 // as the canonical one (the range-limited path has none), for encoders that do
 // not look at NaNs.
 template <bool CLAMP, bool CANON_M, bool CANON_W>
@@ -447,15 +449,14 @@ __device__ __forceinline__ bool step_four(const float (&w)[4], f4 g, f4& m, f4& 
     v[k] = b;
     ve[k] = c;
   }
+  float hi = __builtin_inff();
   if (f.usable) {  // uniform
-    float lo = madd_exact::kTwo60, hi = 0.0f;
+    float lo = madd_exact::kTwo60;
+    hi = 0.0f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       wn[k] = weight_elem_fast<CLAMP>(w[k], ge[k], m[k], v[k], ve[k], s, f, lo, hi);
     ok = lo >= madd_exact::kTwoM100 && hi < madd_exact::kTwo60;
-    // Look at each element: a wave with one group on the general path pays for
-    // both (41M elements, 1% of them zero, bf16 moments: E4M3 118.7 us, 166 if
-    // they fell back, 135 with the general path alone; bf16 132, 161 and 133).
     if (__builtin_expect(!ok, 0)) {
       ok = hi < madd_exact::kTwo60;
 #pragma unroll
@@ -465,15 +466,31 @@ __device__ __forceinline__ bool step_four(const float (&w)[4], f4 g, f4& m, f4& 
                      (fabsf(wn[k]) > madd_exact::kTwoM126 || s.SA * m[k] == 0.0f)));
     }
   }
+  // A wave with one group here pays for both forms; groups that only hold zero
+  // weights with a denormal u_a take the general u_a alone.  41M elements, bf16
+  // moments, us (general form for all / for every group that fails the group
+  // guard / this): 1% zero weights, E4M3 135 / 166 / 119; half of the elements in
+  // rows without a gradient whose moments have decayed to denormals, E4M3
+  // 137 / 159 / 127, NVFP4 179 / 189 / 158.
   if (__builtin_expect(!ok, 0)) {
+    bool zeros = hi < madd_exact::kTwo60;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      zeros = zeros && (fabsf(wn[k]) >= madd_exact::kTwoM100 || w[k] == 0.0f);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      wn[k] = weight_elem<CLAMP>(w[k], ge[k], m[k], v[k], ve[k], s);
-      if (CANON_W) wn[k] = canon_nan(wn[k]);
-      if (CANON_M) {
-        m[k] = canon_nan(m[k]);
-        v[k] = canon_nan(v[k]);
-        ve[k] = canon_nan(ve[k]);
+      const float ua = add_update(m[k], v[k], s);
+      if (!zeros) {
+        wn[k] = weight_elem<CLAMP>(w[k], ge[k], ua, ve[k], s);
+        if (CANON_W) wn[k] = canon_nan(wn[k]);
+        if (CANON_M) {
+          m[k] = canon_nan(m[k]);
+          v[k] = canon_nan(v[k]);
+          ve[k] = canon_nan(ve[k]);
+        }
+      } else if (w[k] == 0.0f) {
+        wn[k] = fmaf(w[k], -(s.LRM * ge[k]), w[k]) + ua;
+        if (CLAMP) wn[k] = clampf(wn[k], -s.WMAX, s.WMAX);
       }
     }
   }

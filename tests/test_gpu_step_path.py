@@ -158,7 +158,15 @@ CASES = {
     "u_a alone, from 2^-126": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
                                m=sign(r, n) * log2_uniform(r, n, -125.99, -96) * ROOT1 / (SA * 0.9)), False),
     "denormal u_a alone": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
-                           m=sign(r, n) * log2_uniform(r, n, -134, -126.01) * ROOT1 / (SA * 0.9)), True),
+                           m=sign(r, n) * log2_uniform(r, n, -139, -126.01) * ROOT1 / (SA * 0.9)), True),
+    "denormal u_a alone, clamps": ({"g_max": 1.0, "w_max": 2.0**-140}, lambda r, n: dict(
+        w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n), v=np.ones(n),
+        m=sign(r, n) * log2_uniform(r, n, -139, -126.01) * ROOT1 / (SA * 0.9)), True),
+    "u_a alone rounds to 0": ({}, lambda r, n: dict({k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g")},
+                              v=np.full(n, 2.0**40), m=sign(r, n) * log2_uniform(r, n, -139, -124)), True),
+    "u_a alone rounds to 0, eta_m < 0": ({"lr_mul": -1e-3}, lambda r, n: dict(
+        {k: np.where(r.random(n) < 0.5, -0.0, 0.0) for k in ("w", "g")},
+        v=np.full(n, 2.0**40), m=sign(r, n) * log2_uniform(r, n, -139, -124)), True),
     "u_a of a denormal SA m": ({}, lambda r, n: dict(w=np.where(r.random(n) < 0.5, -0.0, 0.0), g=np.zeros(n),
                                v=log2_uniform(r, n, -46, -40), m=sign(r, n) * log2_uniform(r, n, -133, -125)), False),
     # zero weights that nothing moves (padding rows, pruned weights): zeros of the right sign

@@ -99,6 +99,19 @@ int32_t madd_probe_step_path(const float* w, const float* g, const float* m, con
                              const float* ve, int64_t quads, const void* scalars, int32_t clamp,
                              float* got, float* general, uint8_t* took, void* stream);
 
+/* The encoders the step's stores are made with (csrc/elem.h: enc_fp8x4,
+ * enc_e2m1x4, enc_bf16x2) against the value grids and the integer rules, on
+ * every fp32 but NaN in every position of a group, stochastically with the
+ * draws on both sides of each element's threshold; for bf16 also the canonical
+ * NaN.
+ * counters: DEVICE array of 9 uint64 values owned by the caller, which the
+ * caller zeroes before the call; on completion they hold the groups that
+ * differ: [0] E4M3 to nearest, [1] E4M3 stochastic, [2], [3] E5M2, [4], [5]
+ * E2M1, [6], [7] bf16 pairs, and [8] the number of groups of four patterns
+ * (2^30, each in four rotations).  Enqueued on `stream`.  Returns 0, -1 for a
+ * NULL pointer, -4 when the launch fails. */
+int32_t madd_check_encoders(uint64_t* counters, void* stream);
+
 /* madd_probe_delay: one wave on `stream` that sleeps `sleeps` times (each
  * s_sleep 127, about 8k cycles, ~3.5 us) and exits.  The benchmark enqueues
  * it ahead of a run of short steps so that the host has queued them all

@@ -152,8 +152,9 @@ __device__ __forceinline__ float dec_fp8(uint32_t c) {
 
 // FP8 codes with gfx950's conversion instructions.  On every fp32 clamped to
 // the largest finite value they are the grid definitions bit for bit, also in
-// the subnormal binades (checked on all 2^32 inputs, the draws on both sides of
-// each input's threshold): RNE by v_cvt_pk_{fp8,bf8}_f32, and
+// the subnormal binades (madd_check_encoders of bench_probes/madd_probes.h: every
+// input but NaN in every position of a group, the draws on both sides of each
+// input's threshold): RNE by v_cvt_pk_{fp8,bf8}_f32, and
 // v_cvt_sr_{fp8,bf8}_f32 with the draw in the high half of its random operand
 // compares it with the top 16 bits of the discarded fraction.  The codes of
 // NaN are left to the caller.  One conversion (8 cycles per wave, two codes per
@@ -236,7 +237,7 @@ __device__ __forceinline__ float dec_e2m1(uint32_t c) {
 }
 
 // E2M1 codes of values already divided by the block scale, not NaN, saturating
-// at +-6, with gfx950's conversions (checked like the FP8 ones).  The
+// at +-6, with gfx950's conversions (checked with the FP8 ones).  The
 // stochastic one draws its second element from other bits of the random
 // operand, so each element takes one, with a zero beside it.
 __device__ __forceinline__ uint32_t cvt_sr_e2m1(float x, uint32_t r16) {  // code in bits 0-3

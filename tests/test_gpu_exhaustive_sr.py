@@ -1,4 +1,6 @@
-"""The step's stochastic rounding on every fp32 input (GPU).  With the weight
+"""The single-element encoder's stochastic rounding on every fp32 input, with
+the draws a step makes (GPU; the group encoders of the step kernels:
+test_gpu_hw_rounding.py).  With the weight
 at 0, eta_a = 1 and eta_m = 0, Appendix B's additive rule (madd_plain_step)
 makes w' = -g exactly for every finite nonzero g (+0 for a zero g, NaN for a
 non-finite one), so feeding all 2^32 fp32 bit patterns as gradients, with

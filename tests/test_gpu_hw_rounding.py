@@ -1,5 +1,7 @@
-"""The bf16 conversion instructions the step kernel rounds with agree with
-the integer definitions of the two roundings on every fp32 input (GPU).
+"""The conversions the step kernels round with agree with the definitions of
+the two roundings on every fp32 input (GPU): the bf16 instructions of the
+single-element encoder, and the step's group encoders (FP8, E2M1, bf16) in every
+position of a group, the draws on both sides of every threshold.
 
 v_cvt_pk_bf16_f32 must equal round-to-nearest-even and v_cvt_sr_bf16_f32,
 given the 16-bit draw in the high half of its random operand, the
@@ -31,3 +33,16 @@ def test_bf16_conversion_instructions_match_the_definitions_exhaustively():
     rne_bad, sr_bad, nan_bad, seen = c.tolist()
     assert seen == 2**32
     assert (rne_bad, sr_bad, nan_bad) == (0, 0, 0)
+
+
+def test_group_encoders_match_the_definitions_exhaustively():
+    B.lib()
+    L = ctypes.CDLL(_build.PROBE_LIB)
+    L.madd_check_encoders.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    L.madd_check_encoders.restype = ctypes.c_int32
+    c = torch.zeros(9, dtype=torch.int64, device="cuda")
+    assert L.madd_check_encoders(c.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    names = [f"{f} {r}" for f in ("e4m3", "e5m2", "e2m1", "bf16") for r in ("rne", "sr")]
+    bad = {k: v for k, v in zip(names, c.tolist()) if v}
+    assert not bad and int(c[8]) == 2**30

@@ -1,6 +1,7 @@
 """Unscaled tensors that start anywhere (GPU): every phase of the global index
 and of the buffers, sizes that end inside a quad or a tile, against the oracle;
-nothing next to the tensor is written."""
+nothing next to the tensor is written (the neighbours hold a pattern that a
+step on zeros does not leave), and the gradients not at all."""
 import numpy as np
 import pytest
 import torch
@@ -13,6 +14,7 @@ from paper_2607_10611_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 PAD = 16
+FILL = 0xA5
 
 
 @pytest.mark.parametrize("wfmt,gfmt,sfmt,rounding", [
@@ -27,8 +29,9 @@ def test_any_start(wfmt, gfmt, sfmt, rounding, n):
     codes = oracle.encode_array(wfmt, x)
     cases = [(p, p, p, p) for p in range(8)] + [(0, 0, 0, 5), (0, 0, 0, 2), (3, 1, 2, 0), (1, 6, 0, 7)]
     for pw, pg, pm, base in cases:
-        def put(a, at):  # the tensor inside a padded buffer, `at` elements in
-            t = torch.zeros(n + 2 * PAD, dtype=to_dev(a[:1]).dtype, device="cuda")
+        def put(a, at):  # the tensor inside a buffer of FILL bytes, `at` elements in
+            dt = to_dev(a[:1]).dtype
+            t = torch.full(((n + 2 * PAD) * dt.itemsize,), FILL, dtype=torch.uint8, device="cuda").view(dt)
             t[at:at + n] = to_dev(a)
             return t, t[at:at + n]
         st = [np.zeros(n, STATE_NP[sfmt]) for _ in range(3)]
@@ -44,8 +47,9 @@ def test_any_start(wfmt, gfmt, sfmt, rounding, n):
             oracle.step(wfmt, hw, gc, *st, hp, gfmt=gfmt, index_base=base + 8 * t, sfmt=sfmt, copy=hc)
         torch.cuda.synchronize()
         tag = f"{wfmt} n={n} phases {pw},{pg},{pm} base {base}"
-        for name, buf, at, ref in [("w", bw, pw, hw), ("copy", bc, pg, hc)] + [
+        for name, buf, at, ref in [("w", bw, pw, hw), ("copy", bc, pg, hc), ("g", bg, pg, gc)] + [
                 (k, b, pm, r) for k, (b, _), r in zip(("m", "v", "ve"), bs, st)]:
             got = to_host(buf).view(ref.dtype)
             assert (got[at:at + n] == ref).all(), f"{tag}: {name}"
-            assert not got[:at].any() and not got[at + n:].any(), f"{tag}: outside {name}"
+            outside = np.concatenate([got[:at], got[at + n:]]).view(np.uint8)
+            assert (outside == FILL).all(), f"{tag}: outside {name}"

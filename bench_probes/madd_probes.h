@@ -75,9 +75,8 @@ int32_t madd_probe_bf16_rounding(uint64_t* counters, void* stream);
  * general operations.
  * counters: DEVICE array of 4 uint64 values owned by the caller, which the
  * caller zeroes before the call; on completion they hold
- *   [0] inputs +-0 and 2^-46 <= x < 2^127 where the square root differs,
- *   [1] inputs 2^-126 <= |x| < 2^126 where the refined reciprocal is not the
- *       one of x's significand, scaled,
+ *   [0] inputs +-0 and finite x >= 2^-46 where the square root differs,
+ *   [1] inputs 2^-126 <= |x| < 2^126 where the refined reciprocal is not 1 / x,
  *   [2] pairs of significands where the quotient differs (every denominator,
  *       1024 numerators each: 512 hashed, 512 around it), and quotients of
  *       -0 that are not -0,
@@ -85,6 +84,13 @@ int32_t madd_probe_bf16_rounding(uint64_t* counters, void* stream);
  * Enqueued on `stream`.  Returns 0, -1 for a NULL pointer, -4 when the
  * launch fails. */
 int32_t madd_check_exact_ops(uint64_t* counters, void* stream);
+
+/* The quotient of csrc/exact.h against the general division: every numerator
+ * significand over the `count` (at most 65536) denominator significands from
+ * `first` on, of 2^23.  counters: DEVICE array of 2 uint64 values owned by the
+ * caller, added to: [0] pairs that differ, [1] pairs examined.  Enqueued on
+ * `stream`.  Returns 0, -1 for an invalid argument, -4 when the launch fails. */
+int32_t madd_check_quotients(int32_t first, int32_t count, uint64_t* counters, void* stream);
 
 /* The step's arithmetic (csrc/elem.h) on `quads` groups of four elements, and
  * which of its two forms each group took.

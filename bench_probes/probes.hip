@@ -155,13 +155,11 @@ __global__ __launch_bounds__(256) void exact_ops_kernel(unsigned long long* c) {
   for (uint32_t j = 0; j < 256u; ++j) {
     const uint32_t u = tid * 256u + j;
     const float x = __uint_as_float(u);
-    if (u == 0u || u == 0x80000000u || (x >= 0x1p-46f && x < 0x1p127f))
+    if (u == 0u || u == 0x80000000u || (x >= 0x1p-46f && u < 0x7F800000u))
       sbad += __float_as_uint(sqrt_in_range(x)) != __float_as_uint(sqrtf(x));
     const uint32_t e = (u >> 23) & 0xFFu;
     if (e >= 1u && e < 253u) {  // 2^-126 <= |x| < 2^126
-      const float one = __uint_as_float((u & 0x807FFFFFu) | 0x3F800000u);
-      rbad += __float_as_uint(recip_in_range(x)) !=
-              __float_as_uint(ldexpf(recip_in_range(one), 127 - (int)e));
+      rbad += __float_as_uint(recip_in_range(x)) != __float_as_uint(1.0f / x);
     }
     ++seen;
   }
@@ -181,6 +179,20 @@ __global__ __launch_bounds__(256) void exact_ops_kernel(unsigned long long* c) {
   if (qbad) atomicAdd(&c[2], qbad);
   for (int off = 32; off >= 1; off >>= 1) seen += __shfl_xor(seen, off);
   if ((threadIdx.x & 63u) == 0u) atomicAdd(&c[3], seen);
+}
+
+// Every numerator significand over one denominator significand per workgroup.
+__global__ __launch_bounds__(256) void quotients_kernel(uint32_t first, unsigned long long* c) {
+  using namespace madd_exact;
+  const float d = __uint_as_float(0x3F800000u | (first + blockIdx.x));
+  const float r = recip_in_range(d);
+  uint32_t bad = 0;
+  for (uint32_t m = threadIdx.x; m < (1u << 23); m += 256u) {
+    const float n = __uint_as_float(0x3F800000u | m);
+    bad += quot_in_range(n, d, r) != n / d;
+  }
+  if (bad) atomicAdd(&c[0], (unsigned long long)bad);
+  if (threadIdx.x == 0) atomicAdd(&c[1], 1ull << 23);
 }
 
 // Plain streams in the step's access shape: a 256-thread workgroup owns one
@@ -253,6 +265,15 @@ extern "C" int32_t madd_check_exact_ops(uint64_t* counters, void* stream) {
   if (!counters) return -1;
   hipLaunchKernelGGL(exact_ops_kernel, dim3(65536), dim3(256), 0, (hipStream_t)stream,
                      (unsigned long long*)counters);
+  return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+extern "C" int32_t madd_check_quotients(int32_t first, int32_t count, uint64_t* counters,
+                                        void* stream) {
+  if (!counters || first < 0 || count < 0 || count > 65536 || first > (1 << 23) - count) return -1;
+  if (count == 0) return 0;
+  hipLaunchKernelGGL(quotients_kernel, dim3((unsigned)count), dim3(256), 0, (hipStream_t)stream,
+                     (uint32_t)first, (unsigned long long*)counters);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 

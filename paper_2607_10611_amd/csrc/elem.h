@@ -369,8 +369,8 @@ __device__ __forceinline__ float weight_elem(float w, float ge, float ua, float 
 // exact.h (142 instead of 254 VALU cycles per element and wave, counted from
 // the measured rates of the instructions).  Powers of two move the
 // intermediates into their ranges: v IBC2 and v_e IBC2 are formed 2^80 times
-// larger (v's smallest denormal becomes 2^-69, and 2^48 the largest root
-// taken), the two numerators SA m and g_e are raised by 2^64, and the factors
+// larger (v's smallest denormal becomes 2^-69, and v IBC2 below 2^48 stays
+// finite), the two numerators SA m and g_e are raised by 2^64, and the factors
 // leave again in operations that are there anyway (the addition of eps, the
 // product with eta_m, the final addition), so that each stays one rounding of
 // the same real number.  Where that is not so:

@@ -8,12 +8,15 @@
 // two neighbours and three selects), at 4 cycles per wave each where an FMA
 // takes 2.  Within the ranges below neither is needed.
 //
-// Both are checked against the general operations by
-// madd_check_exact_ops (bench_probes/madd_probes.h): the square root on every
-// fp32 of its range, the refined reciprocal on every denominator of its range
-// (its significand does not depend on the exponent), the quotient on every
-// denominator significand with a set of numerators; a run over all 2^46 pairs
-// of significands found no difference.
+// The square root is one Newton step from the reciprocal root, the division
+// Markstein's: a refined reciprocal, the quotient's residual and one correction
+// (P. Markstein, Computation of elementary functions on the IBM RISC System/6000
+// processor, IBM J. Res. Dev. 34, 1990), with the instruction's approximations to
+// start from.  Whether that rounds correctly depends on those, so it is checked
+// against the general operations (bench_probes/madd_probes.h): the square root
+// and the reciprocal on every fp32 of their ranges, the quotient on every
+// denominator significand with 1024 numerators each (madd_check_exact_ops) and,
+// by madd_check_quotients, on every pair of significands.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,7 +35,7 @@ constexpr float kTwoM100 = kTwoM60 / 1099511627776.0f;
 constexpr float kTwoM126 = kTwoM64 * kTwoM60 / 4.0f;
 constexpr float kTwoM40 = 1.0f / 1099511627776.0f;
 
-// sqrt(x) for x = 0 or 2^-46 <= x < 2^127.  Smaller positive x give at most
+// sqrt(x) for x = 0 or a finite x >= 2^-46.  Smaller positive x give at most
 // 1.5 sqrt(x); x = -0 gives -0; x <= -2^-71, NaN and Inf give NaN.  The term
 // added below the reciprocal root's argument keeps it finite at 0 and is less
 // than half a unit in the last place of x from 2^-46 on.

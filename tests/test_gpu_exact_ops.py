@@ -3,7 +3,8 @@ the line between that path and the general one (GPU).
 
 madd_check_exact_ops compares the operations with the general ones: the
 square root and the reciprocal on every fp32 of their ranges, the quotient on
-every denominator significand.  The step test mixes weights, gradients and
+every denominator significand with 1024 numerators, and madd_check_quotients on
+slices of them with all.  The step test mixes weights, gradients and
 moments from the denormals to the largest values, zeros of both signs,
 infinities and NaN within each group of four and expects the oracle's bits;
 most such groups take the general path (test_gpu_step_path.py places one
@@ -32,6 +33,22 @@ def test_range_limited_operations_match_the_general_ones():
     assert L.madd_check_exact_ops(c.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert c.tolist() == [0, 0, 0, 2**32]
+
+
+def test_quotients_of_whole_slices_of_significands():
+    """Every numerator over 1024 denominators next to 1, 1.5 and 2 and in between
+    (all 2^23 denominators: 128 calls of 65536, half a minute)."""
+    L = ctypes.CDLL(_build.PROBE_LIB)
+    L.madd_check_quotients.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+    L.madd_check_quotients.restype = ctypes.c_int32
+    c = torch.zeros(2, dtype=torch.int64, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    firsts = (0, 1234567, (1 << 22) - 512, 7654321, (1 << 23) - 1024)
+    for first in firsts:
+        assert L.madd_check_quotients(first, 1024, c.data_ptr(), stream) == 0
+    assert L.madd_check_quotients((1 << 23) - 1023, 1024, c.data_ptr(), stream) == -1
+    torch.cuda.synchronize()
+    assert c.tolist() == [0, len(firsts) * 1024 * 2**23]
 
 
 EXPS = (-149, -140, -127, -126, -125, -110, -101, -100, -99, -90, -82, -71, -70, -64, -63, -60,

@@ -218,8 +218,8 @@ int32_t madd_encode_weights(const float* x, void* w, int32_t wfmt, void* scales,
  *           when block-scaled) rounded to nearest-even -- the BF16 copy the
  *           next step's GEMMs read, which the paper's FP8-master dataflow
  *           (Appendix figure) rebuilds from the stored weights after every
- *           update; here the same pass writes it.  16-byte aligned for the
- *           fast path.
+ *           update; here the same pass writes it.  16-byte aligned with block
+ *           scales; any element otherwise.
  * scales  : NULL, or the block scales of block-scaled FP8, MXFP4 or NVFP4
  *           as in madd_encode_weights (required for the 4-bit formats): the
  *           weight is payload * scale (fp32 product); after the update each
@@ -247,8 +247,8 @@ int32_t madd_encode_weights(const float* x, void* w, int32_t wfmt, void* scales,
  *           a loop of madd_step calls whose bases are the prefix sums of the
  *           sizes is bit-identical to one madd_multi_tensor_step call, and to
  *           any split of the index space (sharding).
- * Unaligned unscaled buffers are accepted and take a slower path with
- * identical results. */
+ * Unscaled buffers may start at any element and any index base, with identical
+ * results; they pay for accesses that cross cache lines. */
 int32_t madd_step(void* w, int32_t wfmt, void* scales, uint16_t* copy, const void* g,
                   int32_t gfmt, void* m, void* v, void* ve, int32_t sfmt, int64_t n,
                   int64_t index_base, const madd_hparams* hp, void* stream);
@@ -381,8 +381,9 @@ int32_t madd_plain_step(void* w, int32_t wfmt, const void* g, int32_t gfmt, int6
  *          draws are the caller's); entries outside [0, n) are skipped.
  * counts : device int32 workspace of n elements (overwritten with cnt).
  * g      : device fp32 output of n elements.
- * Three launches on `stream` (clear counts, count with integer atomics, the
- * gradient); results do not depend on the order of the samples.  Arrays
+ * One launch on `stream` for up to 16384 samples and 131072 entries, else three
+ * (clear counts, count with integer atomics, the gradient); results are the
+ * same and do not depend on the order of the samples.  Arrays
  * must not overlap (MADD_EINVAL). */
 int32_t madd_toy_gradient(const void* w, int32_t wfmt, const float* target, const float* c,
                           const int64_t* idx, int64_t batch, int64_t n, int32_t* counts,

@@ -393,6 +393,11 @@ struct FastScalars {
   bool usable;
 };
 
+// Hyper-parameters outside `usable` (eps = 0 among them) take the general form
+// in every group; 41M elements with eps = 1e-15 are 0.72-1.00 of the time that the
+// kernels with the general form alone and the compiler's wave counts took, over
+// 54 combinations of formats, moments and copies.
+//
 // Uniform, on the scalar unit: positive floats order like their bits, and a
 // normal float times 2^k is k added to its exponent field.
 __device__ __forceinline__ FastScalars fast_scalars(const Scalars& s) {

@@ -400,12 +400,13 @@ __device__ __forceinline__ TensorDesc find_tensor(const TensorDesc* __restrict__
 // The chunk of a workgroup.  Workgroups go round the 8 XCDs in launch order;
 // here each XCD takes runs of kXcdRun consecutive chunks (128 KiB of every
 // fp32 array), so that the XCDs stream from places apart instead of from
-// neighbouring lines of the same HBM pages.  Together with 3 waves per SIMD
-// this takes the 1.1B list with fp32 moments from 6.14-6.37 to 5.71-5.90 ms in
-// bf16 and from 5.75-6.09 to 5.29-5.36 ms in E4M3 (six buffer placements, in
-// turn in one process; runs of 8, 10, 12, 20, 24, 32, 48 and 64 chunks:
-// 5.82-6.42 and 5.22-5.69 ms); the lists of FP8 and NVFP4 masters from 4.30 to
-// 4.16 and from 4.17 to 4.06 ms, NVFP4 with current scaling 9.03 to 8.57 ms.
+// neighbouring lines of the same HBM pages.  1.1B list, fp32 moments, four
+// buffer placements, in turn in one process (ms): bf16 5.70-5.92 against
+// 6.15-6.61 in launch order, E4M3 5.14-5.32 against 5.66-5.79; runs of 8, 10,
+// 12, 20, 24, 32, 48 and 64 chunks: 5.82-6.42 and 5.22-5.69.  With three waves
+// per SIMD as well (kStepWaves) the two are 0.87-0.94 and 0.88-0.90 of the same
+// kernel without either; the lists of FP8 and NVFP4 masters went from 4.30 to
+// 4.16 and from 4.17 to 4.06 ms, NVFP4 with current scaling from 9.03 to 8.57.
 constexpr uint32_t kXcds = 8, kXcdRun = 16;
 __device__ __forceinline__ int64_t xcd_chunk(uint32_t b, uint32_t n) {
   constexpr uint32_t span = kXcds * kXcdRun;
@@ -447,12 +448,15 @@ __device__ __forceinline__ void store_part(const Quad<WF>& q, const TensorDesc& 
 
 // Waves per SIMD of the step kernel.  With fp32 moments the step is bound by
 // HBM, and three waves' loads are enough to fill it; more only spread the
-// requests over more pages (1.1B list, bf16, in xcd_chunk's order: 2 waves
-// 5.74-5.80 ms, 3 waves 5.69, 4 waves 5.81-5.84, 5 waves 5.89-5.92).  bf16
+// requests over more pages (1.1B list in xcd_chunk's order, ms: bf16 5.70-5.92
+// with 3 waves, 5.93-6.09 with 5; E4M3 5.14-5.32 and 5.46-5.57; in an earlier
+// sweep of bf16 2 waves 5.74-5.80, 3 waves 5.69, 4 waves 5.81-5.84).  bf16
 // moments halve the bytes, and the arithmetic between a wave's loads and
 // stores wants more of them: 5 (at most 96 VGPRs; GPT-2-small list 0.380 ms, 3
 // waves 0.404; with stochastic rounding, four draws per element, the 1.1B list
 // takes 3.63 ms with 5, 3.71 with 4, 3.67 with 6 and 4.59, spilling, with 7).
+// At 5 the stochastic moments with stochastic weights and a compute copy or
+// clamps spill 2-7 registers; nothing else does.
 template <int SF>
 constexpr int kStepWaves = SF == SF_FP32 ? 3 : 5;
 
@@ -666,11 +670,12 @@ __device__ __forceinline__ uint32_t requant_quad(Quad<WF>& q, const float (&wn)[
 }
 
 // Waves per SIMD of the block kernel, which holds two quads and their block
-// factors through the re-quantization: 4 where its 128 VGPRs do (1.1B list, FP8
-// masters, bf16 moments: 3.59 ms with 4, 3.83 with the compiler's 3, 6.40,
-// spilling, with 5), 3 with the stochastic moments' draws (16 layers, FP8
-// masters: 2.99 ms, 4.44 with 4) and where fp32 moments bind it to HBM (4.46
-// and 4.60 ms).
+// factors through the re-quantization: 4 (128 VGPRs) with bf16 moments (1.1B
+// list, FP8 masters: 3.59 ms with 4, 3.83 with the compiler's 3, 6.40,
+// spilling, with 5; of the 4-wave kernels only NVFP4's with stochastic weights,
+// clamps and a compute copy spills, 8 registers), 3 with the stochastic moments'
+// draws (16 layers, FP8 masters: 2.99 ms, 4.44 with 4) and where fp32 moments
+// bind it to HBM (4.46 and 4.60 ms).
 template <int SF>
 constexpr int kBlockWaves = SF == SF_BF16 ? 4 : 3;
 
@@ -1576,8 +1581,9 @@ int32_t launch(step_fn fn, const TensorDesc* table, int ntab, const TensorDesc& 
 // step from 39.3 ms (one group) to 38.8 ms (65536: 40.9; 98304: 43.7).
 //
 // With the range-limited arithmetic and xcd_chunk's order the 7B list takes
-// 42.1-42.5 ms (32768: 43.8-44.4), the 1.1B list 8.33 (32768: 7.79; 24576:
-// 7.99; 57344: 7.94; 81920: 8.17; 16384: 8.64): no one size is best for both.
+// 42.1-42.5 ms with 40960 chunks (32768: 43.8-44.4), the 1.1B list 8.33 (32768:
+// 7.79; 24576: 7.99; 57344: 7.94; 81920: 8.17; 16384: 8.64).  No one size is
+// best for both: the constant is the 7B list's, and costs the 1.1B list 7%.
 constexpr int64_t kNvcsGroupChunks = 40960;
 
 int32_t launch_nvcs(const NvcsKernels& k, const TensorDesc* table, int ntab,

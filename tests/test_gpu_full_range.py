@@ -141,7 +141,8 @@ def test_full_range_bf16_moments(wfmt, sfmt, state, grads):
 
 
 def test_full_range_unaligned_index_base_per_element_path():
-    """The per-element path (index base not a multiple of 8)."""
+    """Tiles shifted by the index base's distance from a multiple of 8, with
+    partial quads in the first and last tile."""
     run("bf16", "fp32", "full", "full", HPARAM_SETS["eps0"], index_base=5, seed=32)
     run("fp32", "fp32", "zero_v", "normal", HPARAM_SETS["late_step_sr"], index_base=3, seed=33)
 

@@ -166,8 +166,8 @@ def test_bf16_moments(wfmt, n):
                                     (3 * 2048 + 1024 + 20, 64), (1024 + 20, 8), (516, 0)])
 def test_aligned_ragged_tails_split_lane_pairs(wfmt, n, base):
     """Aligned index bases with a last tile that ends inside a lane pair's
-    group of sub-tile A or B: the pair must take the per-element path
-    together (the two lanes share Philox blocks)."""
+    group of sub-tile A or B: both lanes draw (they share Philox blocks), and
+    the quad over the end is loaded and stored element by element."""
     run_pair(wfmt, n, 3, 70 + n, dict(rounding="sr", seed=91), index_base=base)
 
 
@@ -258,7 +258,7 @@ def test_unaligned_buffers_take_the_scalar_path():
 
 
 def test_unaligned_buffers_bf16_sr_moments():
-    # the per-element path's moment draws (streams 1-3)
+    # the moment draws (streams 1-3) of quads at any address
     n = 3000
     rng = np.random.default_rng(62)
     codes = encode_both("bf16", random_weights(rng, n + 1, "bf16"))

@@ -394,7 +394,7 @@ struct FastScalars {
 };
 
 // Hyper-parameters outside `usable` (eps = 0 among them) take the general form
-// in every group; 41M elements with eps = 1e-15 are 0.72-1.00 of the time that the
+// in every group; 41M elements with eps = 1e-15 are 0.71-1.01 of the time that the
 // kernels with the general form alone and the compiler's wave counts took, over
 // 54 combinations of formats, moments and copies.
 //

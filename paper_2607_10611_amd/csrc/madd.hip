@@ -1570,20 +1570,15 @@ int32_t launch(step_fn fn, const TensorDesc* table, int ntab, const TensorDesc& 
 // list of G groups takes G + 1 launches after the clear.  `descs` holds the
 // launch's tensors in table order (null for the single tensor of madd_step).
 //
-// Measured on the 7B list's NVFP4 linear layers (same process): with fp32
-// moments pass 1 is bound by HBM and pass 2 by VALU, and overlapping them
-// takes the step from 47.2 ms (one group) to 43.8 ms with groups of at
-// least 40960 chunks (two groups per transformer layer; 36864-49152: within
-// 0.2 ms; 57344 and 65536: 45.2-45.5; 16384: 49.0, launch tails).  Keeping
-// w' in the Infinity Cache between the passes (temporal stores and loads,
-// pass 2 reading its group newest first) gained at most 0.3% more.  With
-// bf16 moments both passes are VALU bound, and the same groups take the
-// step from 39.3 ms (one group) to 38.8 ms (65536: 40.9; 98304: 43.7).
-//
-// With the range-limited arithmetic and xcd_chunk's order the 7B list takes
-// 42.1-42.5 ms with 40960 chunks (32768: 43.8-44.4), the 1.1B list 8.33 (32768:
-// 7.79; 24576: 7.99; 57344: 7.94; 81920: 8.17; 16384: 8.64).  No one size is
-// best for both: the constant is the 7B list's, and costs the 1.1B list 7%.
+// With fp32 moments pass 1 is bound by HBM and pass 2 by its arithmetic, so one
+// runs beside the other; small groups lose more to launch tails.  7B list's
+// NVFP4 linear layers, ms with 40960 chunks (two groups per transformer layer)
+// / 24576 / 32768 / 57344: fp32 moments 41.9-42.0 / 42.4 / 43.0 / 43.1, bf16
+// 32.5-32.8 / 32.5 / 33.1 / 34.0.  1.1B list, fp32 moments: 7.82-7.86 / 7.55-7.61
+// / 7.41-7.47 / 7.52-7.57 (16384: 7.97-8.02; 81920: 7.69-7.74).  No one size is
+// best for both; the constant is the 7B list's and costs the 1.1B list 5%.
+// Keeping w' in the Infinity Cache between the passes (temporal stores and
+// loads, pass 2 reading its group newest first) gained at most 0.3% more.
 constexpr int64_t kNvcsGroupChunks = 40960;
 
 int32_t launch_nvcs(const NvcsKernels& k, const TensorDesc* table, int ntab,

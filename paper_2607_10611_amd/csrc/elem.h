@@ -438,9 +438,9 @@ __device__ __forceinline__ float weight_elem_fast(float w, float ge, float m, fl
 
 // The step of four elements: m, v, v_e updated in place, the new weights.
 // Where the range-limited arithmetic does not vouch for all four, the general
-// one takes them again; true if it did.  CANON: NaNs of the moments and the new weights leave
-// as the canonical one (the range-limited path has none), for encoders that do
-// not look at NaNs.
+// one takes them again; true if it did.  CANON: NaNs of the moments and the new
+// weights leave as the canonical one (the range-limited path has none), for
+// encoders that do not look at NaNs.
 template <bool CLAMP, bool CANON_M, bool CANON_W>
 __device__ __forceinline__ bool step_four(const float (&w)[4], f4 g, f4& m, f4& v, f4& ve,
                                           float (&wn)[4], const Scalars& s) {
